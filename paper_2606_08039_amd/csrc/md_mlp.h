@@ -17,7 +17,6 @@ constexpr int MLP_NORM = 2 * MLP_IN + 2 * MLP_OUT;  // x_mean, x_inv_std, y_mean
 extern const int kParamOff[8];
 
 std::string hip_msg(const char *what, hipError_t e);
-hipError_t mlp_destandardize(const float *Y, const float *ymean_std, float *out, int B, hipStream_t st);
 const float *mlp_device_params(const md_mlp *m);
 const float *mlp_device_norm(const md_mlp *m);
 

@@ -328,8 +328,8 @@ MD_MLP_NOALLOC_MAX_BATCH = 4096
 
 
 def md_mlp_forward_noalloc(m, X, Y, B=None, stream=None):
-    """md_mlp_forward with its intermediates in the library's static device
-    buffer (allocates nothing); Y [B][6] float32 receives the outputs."""
+    """md_mlp_forward with its intermediates on chip (allocates nothing, keeps
+    nothing); Y [B][6] float32 receives the outputs."""
     B = X.shape[0] if B is None else B
     mlp_check(lib().md_mlp_forward_noalloc(m, _VP(X.data_ptr()), int(B), _VP(Y.data_ptr()),
                                            _stream_ptr(stream)), m)
