@@ -312,6 +312,16 @@ md_status prepare_launch(md_ctx *ctx) {
     return build_bins(ctx, slots_for(ctx, ctx->cfg), bin_mode_for(ctx, ctx->cfg), &bs);
 }
 
+// The step kernel of the context's integrator and disturbances.
+template <int ACT>
+static hipError_t launch_act(const md_ctx *ctx, const StepArgs &a, const LaunchCfg &cfg, const BinSet &bs,
+                             hipStream_t st) {
+    if (ctx->integ == MD_INTEG_RK4) return launch_step_rk4<ACT>(a, ctx->mask, cfg, bs.n_bins, bs.slots, st);
+    if (ctx->dr_on) return launch_step_dr<ACT>(a, ctx->mask, cfg, bs.n_bins, bs.slots, st);
+    if (ctx->wind.models) return launch_step_wind<ACT>(a, ctx->mask, cfg, bs.n_bins, bs.slots, st);
+    return launch_step<ACT>(a, ctx->mask, cfg, bs.n_bins, bs.slots, st);
+}
+
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,
                  const LaunchCfg &cfg) {
@@ -333,10 +343,14 @@ md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int acti
     a.N = ctx->n_drones;
     a.bins = BinTables{bs->d_slot, bs->d_mmax};
     a.tstride = pair_stride(ctx->max_m);
-    hipError_t e = (ctx->integ == MD_INTEG_RK4) ? launch_step_rk4(a, ctx->mask, ctx->act, cfg, bs->n_bins, bs->slots, st)
-                   : ctx->dr_on ? launch_step_dr(a, ctx->mask, ctx->act, cfg, bs->n_bins, bs->slots, st)
-                   : ctx->wind.models ? launch_step_wind(a, ctx->mask, ctx->act, cfg, bs->n_bins, bs->slots, st)
-                                      : launch_step(a, ctx->mask, ctx->act, cfg, bs->n_bins, bs->slots, st);
+    hipError_t e = hipSuccess;
+    switch (ctx->act) {
+        case 0: e = launch_act<0>(ctx, a, cfg, *bs, st); break;
+        case 1: e = launch_act<1>(ctx, a, cfg, *bs, st); break;
+        case 2: e = launch_act<2>(ctx, a, cfg, *bs, st); break;
+        case 3: e = launch_act<3>(ctx, a, cfg, *bs, st); break;
+        default: e = launch_act<4>(ctx, a, cfg, *bs, st); break;
+    }
     if (e != hipSuccess) {
         ctx->err = hip_msg("step kernel launch", e);
         return MD_E_HIP;

@@ -13,6 +13,7 @@
 // with the rotation of a stage taken from its normalised quaternion; the
 // quaternion is renormalised after the step.  One lane per drone; the
 // neighbour sweep is the all-pairs or one of the pair-symmetric ones.
+// Compiled once per action type (MD_ACT).
 #include "md_sweep.h"
 
 namespace md {
@@ -256,20 +257,15 @@ hipError_t launch_m(const StepArgs &a, uint32_t mask, const LaunchCfg &cfg, int 
 
 }  // namespace
 
-hipError_t launch_step_rk4(const StepArgs &a, uint32_t mask, int act, const LaunchCfg &cfg,
-                           int n_bins, int slots, hipStream_t stream) {
+template <>
+hipError_t launch_step_rk4<MD_ACT>(const StepArgs &a, uint32_t mask, const LaunchCfg &cfg, int n_bins, int slots,
+                                   hipStream_t stream) {
     if (n_bins <= 0 || a.n_steps <= 0) return hipSuccess;
     if ((mask & 4u) && cfg.lpd != 1) return hipErrorInvalidValue;
     const int threads = slots;
     size_t lds = (mask & 4u) ? sizeof(float4) * 2 * 2 * (size_t)slots : 0;
     if ((mask & 4u) && cfg.sym == 1) lds += sizeof(float) * (size_t)slots * (size_t)a.tstride;
-    switch (act) {
-        case 0: return launch_m<0>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 1: return launch_m<1>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 2: return launch_m<2>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 3: return launch_m<3>(a, mask, cfg, n_bins, threads, lds, stream);
-        default: return launch_m<4>(a, mask, cfg, n_bins, threads, lds, stream);
-    }
+    return launch_m<MD_ACT>(a, mask, cfg, n_bins, threads, lds, stream);
 }
 
 }  // namespace md

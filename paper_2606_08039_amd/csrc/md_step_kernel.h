@@ -669,21 +669,15 @@ hipError_t launch_m(const StepArgs &a, uint32_t mask, const LaunchCfg &cfg, int 
     }
 }
 
-template <int DIST>
-hipError_t launch_step_t(const StepArgs &a, uint32_t mask, int act, const LaunchCfg &cfg, int n_bins,
-                         int slots, hipStream_t stream) {
+template <int ACT, int DIST>
+hipError_t launch_step_t(const StepArgs &a, uint32_t mask, const LaunchCfg &cfg, int n_bins, int slots,
+                         hipStream_t stream) {
     if (n_bins <= 0 || a.n_steps <= 0) return hipSuccess;
     const int lpd = (mask & 4u) ? cfg.lpd : 1;
     const int threads = slots * lpd;
     size_t lds = (mask & 4u) ? sizeof(float4) * 2 * 2 * (size_t)slots : 0;
     if ((mask & 4u) && cfg.sym == 1) lds += sizeof(float) * (size_t)slots * (size_t)a.tstride;
-    switch (act) {
-        case 0: return launch_m<0, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 1: return launch_m<1, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 2: return launch_m<2, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
-        case 3: return launch_m<3, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
-        default: return launch_m<4, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
-    }
+    return launch_m<ACT, DIST>(a, mask, cfg, n_bins, threads, lds, stream);
 }
 
 }  // namespace

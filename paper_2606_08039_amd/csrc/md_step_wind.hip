@@ -1,13 +1,15 @@
 // md_step_wind.hip -- instantiation of the persistent step kernel
 // (md_step_kernel.h) with wind and the nominal constants: the wind state and
 // its Philox draws without the randomisation's per-drone registers.
+// Compiled once per action type (MD_ACT).
 #include "md_step_kernel.h"
 
 namespace md {
 
-hipError_t launch_step_wind(const StepArgs &a, uint32_t mask, int act, const LaunchCfg &cfg,
-                            int n_bins, int slots, hipStream_t stream) {
-    return launch_step_t<1>(a, mask, act, cfg, n_bins, slots, stream);
+template <>
+hipError_t launch_step_wind<MD_ACT>(const StepArgs &a, uint32_t mask, const LaunchCfg &cfg,
+                                    int n_bins, int slots, hipStream_t stream) {
+    return launch_step_t<MD_ACT, 1>(a, mask, cfg, n_bins, slots, stream);
 }
 
 }  // namespace md
