@@ -95,18 +95,20 @@ KConst make_kconst(const md_params &p, const md_derived &d, double dt, int decim
     return c;
 }
 
-// Best-fit-decreasing packing of environments into bins of `slots` drone
-// slots; environments larger than a bin are rejected by the caller.  Each
-// environment occupies a contiguous run of slots.  Bins are ordered by their
-// largest environment, heaviest first, so the longest neighbour sweeps start
-// first.
+// Best-fit-decreasing packing of the environments of min_m < M <= max_m drones
+// into bins of `slots` drone slots; environments larger than a bin are
+// rejected by the caller.  Each environment occupies a contiguous run of
+// slots, a multiple of `granule` of them (the idle ones know their
+// environment).  Bins are ordered by their largest environment, heaviest
+// first, so the longest neighbour sweeps start first.
 static void pack_bins(const std::vector<int32_t> &off, int slots, std::vector<int2> &tab,
-                      std::vector<int> &mmax, int &n_bins) {
+                      std::vector<int> &mmax, int &n_bins, int granule = 1, int min_m = 0, int max_m = 1 << 20) {
+    auto room = [&](int m) { return (m + granule - 1) / granule * granule; };
     const int E = (int)off.size() - 1;
     std::vector<int> order;
     order.reserve(E);
     for (int e = 0; e < E; ++e)
-        if (off[e + 1] > off[e]) order.push_back(e);
+        if (off[e + 1] - off[e] > min_m && off[e + 1] - off[e] <= max_m) order.push_back(e);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return (off[a + 1] - off[a]) > (off[b + 1] - off[b]);
     });
@@ -119,7 +121,7 @@ static void pack_bins(const std::vector<int32_t> &off, int slots, std::vector<in
     for (int e : order) {
         const int m = off[e + 1] - off[e];
         int pick = -1;
-        for (int f = m; f <= slots && pick < 0; ++f) {
+        for (int f = room(m); f <= slots && pick < 0; ++f) {
             while (!by_free[f].empty()) {
                 const int b = by_free[f].back();
                 by_free[f].pop_back();
@@ -135,7 +137,7 @@ static void pack_bins(const std::vector<int32_t> &off, int slots, std::vector<in
         }
         Bin &B = bins[pick];
         B.envs.push_back(e);
-        B.used += m;
+        B.used += room(m);
         B.mmax = std::max(B.mmax, m);
         by_free[slots - B.used].push_back(pick);
     }
@@ -154,11 +156,26 @@ static void pack_bins(const std::vector<int32_t> &off, int slots, std::vector<in
         int lo = 0;
         for (int e : B.envs) {
             const int m = off[e + 1] - off[e];
-            for (int t = 0; t < m; ++t)
-                tab[(size_t)ob * slots + lo + t] = make_int2(off[e] + t, (lo << 16) | m);
-            lo += m;
+            for (int t = 0; t < room(m); ++t)
+                tab[(size_t)ob * slots + lo + t] = make_int2(t < m ? off[e] + t : -1, (lo << 16) | m);
+            lo += room(m);
         }
     }
+}
+
+// Bins for the block-symmetric sweep: the environments of more than
+// BLOCK_MIN_ENV drones in whole waves, then the others, packed.
+static void pack_bins_whole_waves(const std::vector<int32_t> &off, int slots, std::vector<int2> &tab,
+                                  std::vector<int> &mmax, int &n_bins) {
+    pack_bins(off, slots, tab, mmax, n_bins, 64, BLOCK_MIN_ENV);
+    for (int &m : mmax) m |= 0x20000;
+    std::vector<int2> t;
+    std::vector<int> mm;
+    int nb = 0;
+    pack_bins(off, slots, t, mm, nb, 1, 0, BLOCK_MIN_ENV);
+    tab.insert(tab.end(), t.begin(), t.end());
+    mmax.insert(mmax.end(), mm.begin(), mm.end());
+    n_bins += nb;
 }
 
 // Bins for the wave-shuffle sweep: environments packed into 64-slot wave
@@ -244,6 +261,8 @@ md_status build_bins(md_ctx *ctx, int slots, int mode, BinSet **out) {
             return MD_E_UNSUPPORTED;
         }
         pack_bins_interleaved(ctx->off, M, slots, tab, mm, bs.n_bins);
+    } else if (mode == BIN_WHOLE_WAVES) {
+        pack_bins_whole_waves(ctx->off, slots, tab, mm, bs.n_bins);
     } else if (mode == BIN_WAVE_ALIGNED) {
         pack_bins_wave_aligned(ctx->off, slots, tab, mm, bs.n_bins);
     } else {
@@ -281,13 +300,26 @@ void free_bins(md_ctx *ctx) {
     ctx->binsets.clear();
 }
 
+// Whether the one-lane all-pairs configuration has environments that take the
+// block-symmetric sweep.
+static bool block_sweep(const md_ctx *ctx, const LaunchCfg &cfg) {
+    return (ctx->mask & MD_AERO_DW) && cfg.lpd == 1 && cfg.sym == 0 && ctx->max_m > BLOCK_MIN_ENV;
+}
+
 int slots_for(const md_ctx *ctx, const LaunchCfg &cfg) {
     const int lpd = (ctx->mask & MD_AERO_DW) ? cfg.lpd : 1;
+    if (block_sweep(ctx, cfg)) {
+        // whole multiples of the largest environment's waves: no wave of a
+        // bin stays idle behind it
+        const int w = (ctx->max_m + 63) / 64;
+        return 64 * w * std::max(1, cfg.waves / w);
+    }
     return 64 * cfg.waves / lpd;
 }
 
 int bin_mode_for(const md_ctx *ctx, const LaunchCfg &cfg) {
     if (!(ctx->mask & MD_AERO_DW)) return BIN_PACKED;
+    if (block_sweep(ctx, cfg)) return BIN_WHOLE_WAVES;
     return cfg.sym == 3 ? BIN_INTERLEAVED : cfg.sym == 2 ? BIN_WAVE_ALIGNED : BIN_PACKED;
 }
 
@@ -343,13 +375,18 @@ md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int acti
     a.N = ctx->n_drones;
     a.bins = BinTables{bs->d_slot, bs->d_mmax};
     a.tstride = pair_stride(ctx->max_m);
+    LaunchCfg how = cfg;
+    if (block_sweep(ctx, cfg)) {
+        how.sym = SWEEP_BLOCK;
+        how.unroll = 1;
+    }
     hipError_t e = hipSuccess;
     switch (ctx->act) {
-        case 0: e = launch_act<0>(ctx, a, cfg, *bs, st); break;
-        case 1: e = launch_act<1>(ctx, a, cfg, *bs, st); break;
-        case 2: e = launch_act<2>(ctx, a, cfg, *bs, st); break;
-        case 3: e = launch_act<3>(ctx, a, cfg, *bs, st); break;
-        default: e = launch_act<4>(ctx, a, cfg, *bs, st); break;
+        case 0: e = launch_act<0>(ctx, a, how, *bs, st); break;
+        case 1: e = launch_act<1>(ctx, a, how, *bs, st); break;
+        case 2: e = launch_act<2>(ctx, a, how, *bs, st); break;
+        case 3: e = launch_act<3>(ctx, a, how, *bs, st); break;
+        default: e = launch_act<4>(ctx, a, how, *bs, st); break;
     }
     if (e != hipSuccess) {
         ctx->err = hip_msg("step kernel launch", e);

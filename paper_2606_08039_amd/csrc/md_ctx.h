@@ -72,9 +72,11 @@ struct md_graph {
 namespace md {
 
 // Packing of environments into bins: contiguous runs (best fit decreasing),
-// contiguous runs that never cross a wavefront, or interleaved inside each
-// wave (uniform power-of-two environments, the rotation sweep).
-enum BinMode { BIN_PACKED = 0, BIN_WAVE_ALIGNED = 1, BIN_INTERLEAVED = 2 };
+// contiguous runs that never cross a wavefront, interleaved inside each wave
+// (uniform power-of-two environments, the rotation sweep), or environments of
+// more than BLOCK_MIN_ENV drones in whole waves, the others packed in bins of
+// their own (the block-symmetric sweep).
+enum BinMode { BIN_PACKED = 0, BIN_WAVE_ALIGNED = 1, BIN_INTERLEAVED = 2, BIN_WHOLE_WAVES = 3 };
 md_status build_bins(md_ctx *ctx, int slots, int mode, BinSet **out);
 void free_bins(md_ctx *ctx);
 int slots_for(const md_ctx *ctx, const LaunchCfg &cfg);

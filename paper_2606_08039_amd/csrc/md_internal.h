@@ -72,8 +72,9 @@ __host__ __device__ constexpr int action_rows(int act) { return act == 4 ? 7 : 4
 //   x = global drone index or -1 for an idle slot,
 //   y = (first slot of the drone's environment inside the bin) << 16 | M_env.
 // Per bin: the largest environment it holds (the uniform neighbour-loop
-// bound) in the low 16 bits, and bit 16 set when every environment in the
-// bin has that size (no per-lane bound check needed).
+// bound) in the low 16 bits, bit 16 set when every environment in the bin has
+// that size (no per-lane bound check needed), and bit 17 set when the bin's
+// environments occupy whole waves (the block-symmetric sweep).
 struct BinTables {
     const int2 *slot;      // [n_bins * slots]
     const int *bin_mmax;   // [n_bins]
@@ -110,8 +111,17 @@ struct LaunchCfg {
     int unroll;  // neighbour-loop unroll: 1, 2, 4 or 8
     int waves;   // waves per workgroup (bin size 64 * waves / lpd slots)
     int sym;     // pair-symmetric sweep (lpd must be 1): 1 LDS term matrix, 2 wave permutes,
-                 // 3 whole-wave rotation on interleaved uniform bins
+                 // 3 whole-wave rotation on interleaved uniform bins; inside the library also
+                 // SWEEP_BLOCK
 };
+
+// The one-lane all-pairs configuration (lpd 1, sym 0) sweeps environments of
+// more than this many drones block by block (dw_block), evaluating each
+// unordered pair once.  The line is where the LDS term matrix (sym 1), which
+// sums in the same order as the all-pairs sweep, no longer fits 64 KB: below
+// it the two stay bitwise equal.
+constexpr int BLOCK_MIN_ENV = 112;
+constexpr int SWEEP_BLOCK = 4;
 
 // The kernels of one action type, each in an object of its own.
 template <int ACT>

@@ -34,7 +34,8 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
     const int menv = tab.y & 0xffff;
     const int mm_word = a.bins.bin_mmax[blockIdx.x];
     const int mmax = mm_word & 0xffff;
-    const bool uniform = (mm_word >> 16) != 0;
+    const bool uniform = ((mm_word >> 16) & 1) != 0;
+    const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
     const int N = a.N;
 
     Drone d{};
@@ -60,6 +61,7 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
         }
     } else {
         d.qw = 1.f;
+        if (block) d.px = d.py = 1e18f;  // out of every drone's reach
     }
 
     float *tmat = (float *)(lds_pos + 4 * slots);
@@ -104,7 +106,12 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
         for (int st = 0; st < 4; ++st) {
             float4 *buf = lds_pos + (st & 1) * (2 * slots);
             if (MASK & 4u) {
-                if (SYM == 3) {
+                if (block) {
+                    // one buffer: the barrier after the sweep ends its reads
+                    const int lane = slot & 63;
+                    float4 *own = lds_pos + 2 * (slot - lane) + lane;
+                    own[0] = own[64] = make_float4(d.px, d.py, d.pz, 0.f);
+                } else if (SYM == 3) {
                     // interleaved uniform bins: each wave's positions twice (128 entries)
                     const int lane = slot & 63;
                     float4 *own = buf + 2 * (slot - lane) + lane;
@@ -130,8 +137,18 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
                 Fy += dy;
                 Fz += dz;
             }
-            if (MASK & 4u)
-                Fz -= c.K1 * dw_sum<1, UNROLL, SYM>(c, buf, tmat, a.tstride, slot, 0, lo, mmax, menv, uniform, d);
+            if (MASK & 4u) {
+                if (block) {
+                    float *sums = (float *)(lds_pos + 2 * slots);
+                    const float part = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d)
+                                                      : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d);
+                    __syncthreads();
+                    Fz -= c.K1 * dw_block_rest(sums, slots, slot, menv, part);
+                } else {
+                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM>(
+                                     c, buf, tmat, a.tstride, slot, 0, lo, mmax, menv, uniform, d);
+                }
+            }
             // time derivative k of the stage
             Drone k;
             k.px = d.vx;
@@ -228,10 +245,13 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
         case 1: return launch_u<MASK, ACT, 1>(a, cfg.unroll, n_bins, threads, lds, st);
         case 2:
         case 3:
+        case SWEEP_BLOCK:
             // the rotation sweep is unrolled in full, the permute sweep not at
             // all (see cfg_valid): one instantiation each
             if (cfg.unroll != 1) return hipErrorInvalidValue;
-            if (cfg.sym == 3)
+            if (cfg.sym == SWEEP_BLOCK)
+                hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, SWEEP_BLOCK>), dim3(n_bins), dim3(threads), lds, st, a);
+            else if (cfg.sym == 3)
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins), dim3(threads), lds, st, a);
             else
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 2>), dim3(n_bins), dim3(threads), lds, st, a);

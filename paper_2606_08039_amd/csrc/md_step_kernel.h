@@ -267,7 +267,8 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
     const int menv = tab.y & 0xffff;
     const int mm_word = a.bins.bin_mmax[blockIdx.x];
     const int mmax = mm_word & 0xffff;
-    const bool uniform = (mm_word >> 16) != 0;
+    const bool uniform = ((mm_word >> 16) & 1) != 0;
+    const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
     const int N = a.N;
     const bool writer = valid && (sub == 0);
 
@@ -294,6 +295,7 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
         }
     } else {
         d.qw = 1.f;
+        if (block) d.px = d.py = 1e18f;  // out of every drone's reach
     }
     // Physical constants of this drone (the nominal ones without randomisation).
     KConst cl = c;
@@ -400,7 +402,12 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
         if (MASK & 4u) {
-            if (SYM == 3) {
+            if (block) {
+                // one buffer: the barrier after the sweep ends its reads
+                const int lane = slot & 63;
+                float4 *own = lds_pos + 2 * (slot - lane) + lane;
+                own[0] = own[64] = make_float4(d.px, d.py, d.pz, 0.f);
+            } else if (SYM == 3) {
                 // interleaved uniform bins: each wave's positions twice (128 entries)
                 const int lane = slot & 63;
                 float4 *own = buf + 2 * (slot - lane) + lane;
@@ -501,8 +508,15 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
                 } else {
                     acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d) : dw_rot<false>(c, own, lane, mmax, d);
                 }
+            } else if (block) {
+                float *sums = (float *)(lds_pos + 2 * slots);
+                acc = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d)
+                                     : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d);
+                __syncthreads();
+                acc = dw_block_rest(sums, slots, slot, menv, acc);
             } else {
-                acc = dw_sum<LPD, UNROLL, SYM>(c, buf, tmat, a.tstride, slot, sub, lo, mmax, menv, uniform, d);
+                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM>(
+                    c, buf, tmat, a.tstride, slot, sub, lo, mmax, menv, uniform, d);
             }
             Fz -= cl.K1 * acc;
         }
@@ -638,7 +652,9 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             // the rotation sweep is unrolled in full, the permute sweep not at
             // all (see cfg_valid): one instantiation each
             if (cfg.unroll != 1) return hipErrorInvalidValue;
-            if (cfg.sym == 3)
+            if (cfg.sym == SWEEP_BLOCK)
+                hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, SWEEP_BLOCK, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
+            else if (cfg.sym == 3)
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
             else
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 2, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
