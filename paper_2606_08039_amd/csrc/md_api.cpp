@@ -62,6 +62,8 @@ KConst make_kconst(const md_params &p, const md_derived &d, double dt, int decim
     c.dz_min = (float)std::max(0.0, p.dw_dz_min);
     c.C2s = (float)(std::sqrt(2.0 * std::log(2.0)) * p.C2);
     c.C3s = (float)(std::sqrt(2.0 * std::log(2.0)) * p.C3);
+    c.C2c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C2);
+    c.C3c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C3);
     for (int k = 0; k < 3; ++k) {
         c.pkp[k] = (float)p.pos_kp[k];
         c.pki[k] = (float)p.pos_ki[k];
@@ -300,27 +302,26 @@ void free_bins(md_ctx *ctx) {
     ctx->binsets.clear();
 }
 
-// Whether the one-lane all-pairs configuration has environments that take the
-// block-symmetric sweep.
-static bool block_sweep(const md_ctx *ctx, const LaunchCfg &cfg) {
-    return (ctx->mask & MD_AERO_DW) && cfg.lpd == 1 && cfg.sym == 0 && ctx->max_m > BLOCK_MIN_ENV;
-}
-
-int slots_for(const md_ctx *ctx, const LaunchCfg &cfg) {
-    const int lpd = (ctx->mask & MD_AERO_DW) ? cfg.lpd : 1;
-    if (block_sweep(ctx, cfg)) {
+// How a configuration is launched: which bins, and the library's own sweeps in
+// place of the one-lane all-pairs one where they are the better way to the
+// same sums.  `choose`: the configuration is the layout's default and not the
+// caller's choice.
+LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
+    LaunchPlan p{cfg, 64 * cfg.waves, BIN_PACKED};
+    if (!(ctx->mask & MD_AERO_DW)) return p;
+    p.slots = 64 * cfg.waves / cfg.lpd;
+    p.mode = cfg.sym == 3 ? BIN_INTERLEAVED : cfg.sym == 2 ? BIN_WAVE_ALIGNED : BIN_PACKED;
+    if (cfg.lpd != 1 || cfg.sym != 0) return p;
+    if (ctx->max_m > BLOCK_MIN_ENV) {
+        p.how.sym = SWEEP_BLOCK;
+        p.how.unroll = 1;
+        p.mode = BIN_WHOLE_WAVES;
         // whole multiples of the largest environment's waves: no wave of a
         // bin stays idle behind it
         const int w = (ctx->max_m + 63) / 64;
-        return 64 * w * std::max(1, cfg.waves / w);
+        p.slots = 64 * w * std::max(1, cfg.waves / w);
     }
-    return 64 * cfg.waves / lpd;
-}
-
-int bin_mode_for(const md_ctx *ctx, const LaunchCfg &cfg) {
-    if (!(ctx->mask & MD_AERO_DW)) return BIN_PACKED;
-    if (block_sweep(ctx, cfg)) return BIN_WHOLE_WAVES;
-    return cfg.sym == 3 ? BIN_INTERLEAVED : cfg.sym == 2 ? BIN_WAVE_ALIGNED : BIN_PACKED;
+    return p;
 }
 
 LaunchCfg default_cfg(const md_ctx *ctx) {
@@ -341,7 +342,8 @@ md_status prepare_launch(md_ctx *ctx) {
         while (64 * waves < ctx->max_m) waves *= 2;
         return build_bins(ctx, 64 * waves, BIN_PACKED, &bs);
     }
-    return build_bins(ctx, slots_for(ctx, ctx->cfg), bin_mode_for(ctx, ctx->cfg), &bs);
+    const LaunchPlan p = plan_for(ctx, ctx->cfg, !ctx->tuned);
+    return build_bins(ctx, p.slots, p.mode, &bs);
 }
 
 // The step kernel of the context's integrator and disturbances.
@@ -356,9 +358,10 @@ static hipError_t launch_act(const md_ctx *ctx, const StepArgs &a, const LaunchC
 
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,
-                 const LaunchCfg &cfg) {
+                 const LaunchCfg &cfg, bool choose) {
     BinSet *bs = nullptr;
-    md_status rc = build_bins(ctx, slots_for(ctx, cfg), bin_mode_for(ctx, cfg), &bs);
+    const LaunchPlan plan = plan_for(ctx, cfg, choose);
+    md_status rc = build_bins(ctx, plan.slots, plan.mode, &bs);
     if (rc != MD_OK) return rc;
     StepArgs a;
     a.c = ctx->kc;
@@ -375,11 +378,7 @@ md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int acti
     a.N = ctx->n_drones;
     a.bins = BinTables{bs->d_slot, bs->d_mmax};
     a.tstride = pair_stride(ctx->max_m);
-    LaunchCfg how = cfg;
-    if (block_sweep(ctx, cfg)) {
-        how.sym = SWEEP_BLOCK;
-        how.unroll = 1;
-    }
+    const LaunchCfg &how = plan.how;
     hipError_t e = hipSuccess;
     switch (ctx->act) {
         case 0: e = launch_act<0>(ctx, a, how, *bs, st); break;
@@ -568,8 +567,8 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
     }
     ctx->has_layout = true;
     ctx->cfg = md::default_cfg(ctx);
-    md::BinSet *bs = nullptr;
-    return md::build_bins(ctx, md::slots_for(ctx, ctx->cfg), md::bin_mode_for(ctx, ctx->cfg), &bs);
+    ctx->tuned = false;
+    return md::prepare_launch(ctx);
 }
 
 md_status md_set_integrator(md_ctx *ctx, int integrator) {
@@ -718,7 +717,7 @@ md_status md_step(md_ctx *ctx, const md_state *s, const float *d_action, int act
                                                                  n_obs_slots, n_steps, step0,
                                                                  (hipStream_t)stream);
     return md::launch(ctx, s, d_action, action_per_step, d_obs, n_obs_slots, n_steps, step0,
-                      (hipStream_t)stream, ctx->cfg);
+                      (hipStream_t)stream, ctx->cfg, !ctx->tuned);
 }
 
 }  // extern "C"

@@ -79,12 +79,16 @@ namespace md {
 enum BinMode { BIN_PACKED = 0, BIN_WAVE_ALIGNED = 1, BIN_INTERLEAVED = 2, BIN_WHOLE_WAVES = 3 };
 md_status build_bins(md_ctx *ctx, int slots, int mode, BinSet **out);
 void free_bins(md_ctx *ctx);
-int slots_for(const md_ctx *ctx, const LaunchCfg &cfg);
-int bin_mode_for(const md_ctx *ctx, const LaunchCfg &cfg);
+// What a launch runs: the sweep and lanes, and the bins (slots, BinMode).
+struct LaunchPlan {
+    LaunchCfg how;
+    int slots, mode;
+};
+LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose);
 LaunchCfg default_cfg(const md_ctx *ctx);
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,
-                 const LaunchCfg &cfg);
+                 const LaunchCfg &cfg, bool choose);
 
 // Build the bin tables the next md_step will use (synchronous uploads).
 md_status prepare_launch(md_ctx *ctx);

@@ -19,6 +19,7 @@ struct KConst {
     float drag_s, c_xy, c_z;              // drag_s = 2 pi / 60         (Eq. 5)
     float K1, C2, C3, dz_min;             // K1 = C1 r_p^2 / 16         (Eq. 6)
     float C2s, C3s;                       // sqrt(2 ln 2) C2, sqrt(2 ln 2) C3
+    float C2c, C3c;                       // sqrt(160) times these (dw_margin)
     float pkp[3], pki[3], pkd[3], p_clamp;
     float akp[3], aki[3], akd[3], a_clamp;
     float dsl_pkp[3], dsl_pki[3], dsl_pkd[3], dsl_p_clamp;

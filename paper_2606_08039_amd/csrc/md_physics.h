@@ -346,6 +346,18 @@ __device__ __forceinline__ float dw_raw(const KConst &c, float d2, float adz) {
 
 __device__ __forceinline__ bool dw_near(float d2) { return d2 < 100.f; }
 
+// Negative when the pair's term may differ from 0 (the sign bit is the test):
+// d2 - 160 beta'^2 - 1.6e-28, which dw_raw's exponent -d2 / (beta'^2 + 1e-30)
+// then keeps above -160.  Where it is not negative, the exponent lies below
+// -159 (a few roundings), 2^x is 0 (the smallest denormal is 2^-149) and so is
+// the term.  A NaN position passes or not; its terms are gated to 0 anyway.
+template <bool DZMIN>
+__device__ __forceinline__ float dw_margin(const KConst &c, float dx, float dy, float adz) {
+    const float dze = DZMIN ? fmaxf(adz, c.dz_min) : adz;
+    const float bc = fmaf(c.C2c, dze, c.C3c);
+    return fmaf(-bc, bc, fmaf(dx, dx, fmaf(dy, dy, -1.6e-28f)));
+}
+
 template <bool DZMIN>
 __device__ __forceinline__ float dw_term(const KConst &c, float dx, float dy, float dz) {
     const float d2 = dw_d2(dx, dy);

@@ -22,7 +22,7 @@ namespace {
 using namespace phys;
 
 template <uint32_t MASK, int ACT, int UNROLL, int SYM>
-__global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
+__global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_kernel(StepArgs a) {
     extern __shared__ float4 lds_pos[];  // [2][2 * slots] positions; then T [slots][tstride] (SYM)
     const KConst &c = a.c;
     const int slots = blockDim.x;
@@ -32,7 +32,9 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
     const bool valid = di >= 0;
     const int lo = tab.y >> 16;
     const int menv = tab.y & 0xffff;
-    const int mm_word = a.bins.bin_mmax[blockIdx.x];
+    // each wave of the rotation sweep is a workgroup of its own (md_step_kernel.h)
+    const int mm_word = a.bins.bin_mmax[SYM == 3 ? 0 : blockIdx.x];
+    if (SYM == 3 && __ballot(valid) == 0ull) return;
     const int mmax = mm_word & 0xffff;
     const bool uniform = ((mm_word >> 16) & 1) != 0;
     const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
@@ -81,6 +83,7 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
         for (int k = 0; k < 4; ++k) sp[k] = a.s.ctl[k * N + di];
     int phase = (ACT >= 1) ? (int)(a.step0 % (long long)c.decim) : 0;
     int oslot = 0;
+    int dense = 0;  // sweeps (stages) to run without tests (see the sparse sweeps)
     const float half_dt = 0.5f * c.dt, sixth_dt = c.dt * (1.f / 6.f);
     for (int step = 0; step < a.n_steps; ++step) {
         // ---- rotor speeds, held over the step
@@ -140,13 +143,17 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
             if (MASK & 4u) {
                 if (block) {
                     float *sums = (float *)(lds_pos + 2 * slots);
-                    const float part = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d)
-                                                      : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d);
+                    const float part = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d, dense)
+                                                      : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d, dense);
                     __syncthreads();
                     Fz -= c.K1 * dw_block_rest(sums, slots, slot, menv, part);
                 } else {
-                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM>(
-                                     c, buf, tmat, a.tstride, slot, 0, lo, mmax, menv, uniform, d);
+                    // the rotation sweep without tests: with them the
+                    // compiler forms the stage's multiply-adds in other
+                    // places than around the permute sweep, and the two are
+                    // to round alike (453 against 470 us, 4096 x 32 drones)
+                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, false>(
+                                     c, buf, tmat, a.tstride, slots, slot, 0, lo, mmax, menv, uniform, d, dense);
                 }
             }
             // time derivative k of the stage
@@ -252,7 +259,8 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, SWEEP_BLOCK>), dim3(n_bins), dim3(threads), lds, st, a);
             else if (cfg.sym == 3)
-                hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins), dim3(threads), lds, st, a);
+                hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins * threads / 64), dim3(64),
+                                   lds * 64 / threads, st, a);
             else
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 2>), dim3(n_bins), dim3(threads), lds, st, a);
             return hipGetLastError();

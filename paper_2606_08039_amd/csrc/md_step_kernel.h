@@ -254,7 +254,8 @@ struct RowSeg {
 // registers per lane that sixteen waves per workgroup leave (they spilled to
 // scratch memory, which the long launches then streamed through HBM).
 template <uint32_t MASK, int ACT, int LPD, int UNROLL, int SYM, int DIST>
-__global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel(StepArgs a) {
+__global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1024,
+                                  SYM == 3 ? (DIST == 2 ? 2 : 4) : 1) step_kernel(StepArgs a) {
     extern __shared__ float4 lds_pos[];  // [2][2 * slots] positions; then T [slots][tstride] (SYM)
     const KConst &c = a.c;
     const int slots = blockDim.x / LPD;
@@ -265,7 +266,14 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
     const bool valid = di >= 0;
     const int lo = tab.y >> 16;
     const int menv = tab.y & 0xffff;
-    const int mm_word = a.bins.bin_mmax[blockIdx.x];
+    // the rotation sweep's waves are independent: each is a workgroup of its
+    // own, whatever the bins' size, and every bin reports the same M.  Larger
+    // groups idle CUs where there are fewer than a few groups per CU (16384 x
+    // 8 drones, 100 steps: 243 us against 310 and 528 us in groups of 8 and 16
+    // waves) and wait for one another's tested pairs (8192 x 32, 1000 steps
+    // with observations: 5.00 ms against 5.28 and 5.15 ms)
+    const int mm_word = a.bins.bin_mmax[SYM == 3 ? 0 : blockIdx.x];
+    if (SYM == 3 && __ballot(valid) == 0ull) return;
     const int mmax = mm_word & 0xffff;
     const bool uniform = ((mm_word >> 16) & 1) != 0;
     const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
@@ -399,6 +407,7 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
     float nprev[4] = {0.f, 0.f, 0.f, 0.f};
     float rpy[3] = {0.f, 0.f, 0.f};  // the previous row's angles
     int pslot = 0;
+    int dense = 0;  // steps to sweep without tests (see the sparse sweeps)
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
         if (MASK & 4u) {
@@ -503,20 +512,20 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
                                      writer ? di * 4 : 20 * N * 4, N * 4,
                                      {d.px, d.py, d.pz, d.qw, d.qx, d.qy, d.qz, rpy[0], rpy[1], rpy[2],
                                       d.vx, d.vy, d.vz, d.wx, d.wy, d.wz, nprev[0], nprev[1], nprev[2], nprev[3]}};
-                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d, seg)
-                                         : dw_rot<false>(c, own, lane, mmax, d, seg);
+                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d, dense, seg)
+                                         : dw_rot<false>(c, own, lane, mmax, d, dense, seg);
                 } else {
-                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d) : dw_rot<false>(c, own, lane, mmax, d);
+                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d, dense) : dw_rot<false>(c, own, lane, mmax, d, dense);
                 }
             } else if (block) {
                 float *sums = (float *)(lds_pos + 2 * slots);
-                acc = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d)
-                                     : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d);
+                acc = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d, dense)
+                                     : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d, dense);
                 __syncthreads();
                 acc = dw_block_rest(sums, slots, slot, menv, acc);
             } else {
                 acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM>(
-                    c, buf, tmat, a.tstride, slot, sub, lo, mmax, menv, uniform, d);
+                    c, buf, tmat, a.tstride, slots, slot, sub, lo, mmax, menv, uniform, d, dense);
             }
             Fz -= cl.K1 * acc;
         }
@@ -655,7 +664,8 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, SWEEP_BLOCK, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
             else if (cfg.sym == 3)
-                hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
+                hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins * threads / 64), dim3(64),
+                                   lds * 64 / threads, st, a);
             else
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 2, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
             return hipGetLastError();

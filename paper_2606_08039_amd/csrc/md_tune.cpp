@@ -81,6 +81,7 @@ static std::vector<LaunchCfg> candidates(const md_ctx *ctx) {
             for (int w : {1, 2, 4, 8, 16})
                 for (int u : {1, 2, 4}) {
                     LaunchCfg c{lpd, u, w, sym};
+                    if (sym == 3 && w > 1) continue;  // its waves run as workgroups of their own
                     if (cfg_valid(ctx, c)) out.push_back(c);
                 }
     return out;
@@ -231,7 +232,7 @@ md_status autotune(md_ctx *ctx, const md_state *s, const float *d_action, int ac
     auto timed = [&](const LaunchCfg &c, float &ms) {
         e = hipEventRecord(a, st);
         if (e != hipSuccess) return;
-        rc = launch(ctx, &ws, d_action, action_per_step, d_obs, d_obs ? n_obs_slots : 0, n_steps, step0, st, c);
+        rc = launch(ctx, &ws, d_action, action_per_step, d_obs, d_obs ? n_obs_slots : 0, n_steps, step0, st, c, false);
         if (rc != MD_OK) return;
         e = hipEventRecord(b, st);
         if (e == hipSuccess) e = hipEventSynchronize(b);
