@@ -320,6 +320,22 @@ LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
         // bin stays idle behind it
         const int w = (ctx->max_m + 63) / 64;
         p.slots = 64 * w * std::max(1, cfg.waves / w);
+    } else if (choose && ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models && ctx->max_m > 1) {
+        // Several lanes per drone where one each would leave SIMDs without a
+        // wave (a wave per SIMD is 65536 lanes).  Measured, us per 100 steps
+        // with 1 / 4 / 8 lanes: M = 32, 8192 drones 221 / 129 / 100, 16384
+        // drones 222 / 128 / 129, 32768 drones 230 / 163 / 202, 65536 drones
+        // 224 / 257 / 361; M = 64, 32768 drones 394 / 256 / 293, 65536 drones
+        // 386 / 406 / 558; M = 8 (a group of eight is nearly empty of other
+        // work), 512 drones 99 / 69 / 74, 32768 drones 104 / 90 / 156.
+        // Workgroups of four waves for the larger environments pack ragged
+        // sizes into 64 slots: 135 against 161 us for 1024 of 2..32 drones.
+        const int lpd = ctx->n_drones <= 10000 && ctx->max_m >= 24 ? 8 : ctx->n_drones <= 40000 ? 4 : 1;
+        const int waves = std::max((ctx->max_m * lpd + 63) / 64, lpd == 4 && ctx->max_m > 16 ? 4 : 1);
+        if (lpd > 1) {
+            p.how = LaunchCfg{lpd, 1, waves, SWEEP_LANES};
+            p.slots = 64 * waves / lpd;
+        }
     }
     return p;
 }

@@ -113,7 +113,7 @@ struct LaunchCfg {
     int waves;   // waves per workgroup (bin size 64 * waves / lpd slots)
     int sym;     // pair-symmetric sweep (lpd must be 1): 1 LDS term matrix, 2 wave permutes,
                  // 3 whole-wave rotation on interleaved uniform bins; inside the library also
-                 // SWEEP_BLOCK
+                 // SWEEP_BLOCK and SWEEP_LANES
 };
 
 // The one-lane all-pairs configuration (lpd 1, sym 0) sweeps environments of
@@ -123,6 +123,9 @@ struct LaunchCfg {
 // it the two stay bitwise equal.
 constexpr int BLOCK_MIN_ENV = 112;
 constexpr int SWEEP_BLOCK = 4;
+// Four or eight lanes per drone that sum as one (dw_lanes), in place of the
+// default configuration's one lane where that leaves the chip idle.
+constexpr int SWEEP_LANES = 5;
 
 // The kernels of one action type, each in an object of its own.
 template <int ACT>

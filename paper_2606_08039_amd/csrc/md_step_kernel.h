@@ -655,6 +655,17 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
         hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 0, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
         return hipGetLastError();
     }
+    if (cfg.sym == SWEEP_LANES) {
+        if constexpr (DIST == 0) {
+            switch (cfg.lpd) {
+                case 4: hipLaunchKernelGGL((step_kernel<MASK, ACT, 4, 1, SWEEP_LANES, DIST>), dim3(n_bins), dim3(threads), lds, st, a); break;
+                case 8: hipLaunchKernelGGL((step_kernel<MASK, ACT, 8, 1, SWEEP_LANES, DIST>), dim3(n_bins), dim3(threads), lds, st, a); break;
+                default: return hipErrorInvalidValue;
+            }
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     if (cfg.sym) {
         if (cfg.lpd != 1) return hipErrorInvalidValue;
         if (cfg.sym >= 2) {

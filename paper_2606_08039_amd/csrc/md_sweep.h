@@ -93,6 +93,67 @@ __device__ __forceinline__ float dw_sweep(const KConst &c0, const float4 *buf, i
     return acc;
 }
 
+// LPD lanes per drone, the sum of the one-lane sweep bit for bit: lane `sub`
+// evaluates every LPD-th candidate, then the group's terms are added one after
+// the other in ascending order, each broadcast to the drone's lanes by a DPP
+// operand of the addition.  With eight lanes the running sum is valid in one
+// quad at a time: a quad adds its four terms, hands the sum to the other one
+// (row_half_mirror), which adds its own four and, in the next group, the
+// first four (the candidates' assignment alternates).  Returned in every lane.
+// For layouts that one lane per drone leaves at a wave per SIMD or less, where
+// a step costs the length of one wave's instruction stream: 64 x 32 drones,
+// 100 steps, 220 us with one lane, 129 with four, 100 with eight; 1024 ragged
+// environments of 2..32 drones 242, 135 and 157 us (eight lanes: 2.3 waves per
+// SIMD).
+template <int CTRL>
+__device__ __forceinline__ float quad_perm(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float half_mirror(float v) {  // lane 7 - i of each eight
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));
+}
+
+template <bool DZMIN, int LPD>
+__device__ __forceinline__ float dw_lanes(const KConst &c0, const float4 *buf, int slots, int lo, int sub, int mmax,
+                                          int menv, const Drone &d) {
+    static_assert(LPD == 4 || LPD == 8, "lanes per drone");
+    const KConst c = pair_consts(c0);
+    float acc = 0.f;
+    auto term = [&](int j) {
+        // (a candidate past the environment is read from the rest of the
+        // buffer, which holds 2 slots entries)
+        const float4 q = buf[min(lo + j, 2 * slots - 1)];
+        const float t = dw_term<DZMIN>(c, q.x - d.px, q.y - d.py, q.z - d.pz);
+        return j < menv ? t : 0.f;
+    };
+    auto add = [&](float t) {
+        acc += quad_perm<0x00>(t);
+        acc += quad_perm<0x55>(t);
+        acc += quad_perm<0xaa>(t);
+        acc += quad_perm<0xff>(t);
+    };
+    // two groups a round: their terms' latencies overlap
+    for (int j = 0; j < mmax; j += 2 * LPD) {
+        const float t0 = term(j + sub), t1 = term(j + LPD + (LPD == 8 ? (sub ^ 4) : sub));
+        add(t0);
+        if (LPD == 8) {
+            acc = half_mirror(acc);
+            add(t0);
+        }
+        add(t1);
+        if (LPD == 8) {
+            acc = half_mirror(acc);
+            add(t1);
+        }
+    }
+    // eight lanes: the first quad holds the sum
+    if (LPD == 8) {
+        const float other = half_mirror(acc);
+        acc = sub < 4 ? acc : other;
+    }
+    return acc;
+}
+
 // Pair-symmetric downwash sweep: each unordered pair of an environment is
 // evaluated once, by lane i for partners (i + d) mod M, d = 1..(M-1)/2, plus
 // d = M/2 from the lower half when M is even.  The term goes to the lower
@@ -511,6 +572,10 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
                                         int sub, int lo, int mmax, int menv, bool uniform, const Drone &d,
                                         int &dense) {
     float acc = 0.f;
+    if constexpr (SYM == SWEEP_LANES) {
+        return c.dz_min > 0.f ? dw_lanes<true, LPD>(c, buf, slots, lo, sub, mmax, menv, d)
+                              : dw_lanes<false, LPD>(c, buf, slots, lo, sub, mmax, menv, d);
+    }
     if (SYM == 3) {
         // interleaved uniform bins (see dw_pairs_rot): `buf` holds each wave's
         // positions twice, 128 entries per wave
