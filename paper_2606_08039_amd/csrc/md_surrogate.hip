@@ -174,6 +174,48 @@ __device__ __forceinline__ void knn_sweep(const float4 *pos, int lo, int m, int 
     }
 }
 
+// The sorted K smallest of a stream of unsigned keys: one more key.
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+template <int K>
+__device__ __forceinline__ void key_insert(uint32_t x, uint32_t (&k)[K]) {
+#pragma unroll
+    for (int t = K - 1; t >= 1; --t) k[t] = med3_u32(k[t - 1], k[t], x);
+    k[0] = min(k[0], x);
+}
+
+// Ranking by keys: a squared distance's bits with the lowest KEY_BITS replaced
+// by the candidate's number, so that one median per slot of the sorted list
+// moves distance and index together (knn_insert's slots take a median, a
+// compare and two selects: 18 against 4.3 cycles).  Keys order candidates as
+// (distance, number) does unless two distances agree in all the other bits;
+// the ninth key is kept to see that, and the caller then ranks the exact way.
+// Distances below KEY_NONE only: the caller checks the positions.
+constexpr int KEY_BITS = 6;
+constexpr uint32_t KEY_MASK = (1u << KEY_BITS) - 1, KEY_NONE = 0x7f000000u;
+
+__device__ __forceinline__ uint32_t knn_key(float d2, int j) { return (__float_as_uint(d2) & ~KEY_MASK) | (uint32_t)j; }
+
+// Neighbours (candidate number + base, or -1) from the nine smallest keys;
+// false if a pair of them cannot be told apart.
+__device__ __forceinline__ bool knn_from_keys(const uint32_t (&k)[KNN + 1], int base, int (&bj)[KNN]) {
+    bool apart = true;
+#pragma unroll
+    for (int t = 0; t < KNN; ++t) {
+        bj[t] = k[t] < KEY_NONE ? base + (int)(k[t] & KEY_MASK) : -1;
+        apart &= (k[t] >> KEY_BITS) != (k[t + 1] >> KEY_BITS) || k[t] >= KEY_NONE;
+    }
+    return apart;
+}
+
+// Whether a drone's squared lateral distances are sure to stay below KEY_NONE
+// (1.7e38); false for non-finite positions.
+__device__ __forceinline__ bool key_range(float px, float py) { return fabsf(px) < 1e18f && fabsf(py) < 1e18f; }
+
 // The 8 nearest from a drone's candidate list: LIST (at most 12) 16-bit slot
 // offsets from lo in ascending order, 2 per word; unused entries hold the
 // drone's own offset (never a member).  Ranking the list in slot order gives
@@ -771,13 +813,26 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
     }
 }
 
+// Floats between the rows of a wave's store stage (16 features of 64 drones).
+constexpr int STAGE_ROW = 20;
+
+// Training samples at the current state.  Bound by the 256-byte feature rows
+// (262144 drones: 100 MB in all, 21 us at the rate of a large copy) once the
+// neighbour ranking is out of the way: rows go through LDS 16 features at a
+// time, so that four lanes store 64 contiguous bytes of a drone (a lane's own
+// 16-byte pieces, 256 bytes from its neighbours', filled a quarter of each
+// 64-byte request), and environments of up to 64 drones rank by keys.  262144
+// drones in environments of 32: 37.5 -> 27.6 us; what is left above the
+// memory's time is one round of load, compute and store per wave, all 4096
+// resident at once.
 __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     const KConst &c = g.c;
     const int S = blockDim.x;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     float4 *pos = (float4 *)smem;  // [2S]
-    float4 *vel = pos + 2 * S;     // [2S]
-    const int slot = threadIdx.x;
+    float4 *vel = pos + 2 * S;     // [S]
+    const int slot = threadIdx.x, lane = slot & 63;
+    float *stage = (float *)(vel + S) + (slot >> 6) * 64 * STAGE_ROW;  // this wave's [64][STAGE_ROW]
     const int2 tab = g.bins.slot[blockIdx.x * S + slot];
     const int di = tab.x;
     const bool valid = di >= 0;
@@ -793,24 +848,52 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     pos[slot] = make_float4(d.px, d.py, d.pz, 0.f);
     vel[slot] = make_float4(d.vx, d.vy, d.vz, 0.f);
     pos[S + slot] = make_float4(0.f, 0.f, 0.f, 0.f);
-    vel[S + slot] = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
-    if (!valid) return;
     float T, tx, ty, tz;
     motor(c, n, T, tx, ty, tz);
     const Rot R = rot_of(d);
     int bj[KNN];
-    {
+    // (bins of more than one wave hold environments of more than 64 drones)
+    bool keyed = S == 64 && __ballot(!key_range(d.px, d.py)) == 0ull;
+    if (keyed) {
+        uint32_t key[KNN + 1];
+#pragma unroll
+        for (int t = 0; t <= KNN; ++t) key[t] = KEY_NONE;
+        for (int jj = 0; jj < mmax; ++jj) {
+            const float d2 = knn_d2(pos[lo + jj], d.px, d.py);
+            key_insert(jj < menv && lo + jj != slot ? knn_key(d2, jj) : KEY_NONE, key);
+        }
+        keyed = __ballot(!knn_from_keys(key, lo, bj)) == 0ull;
+    }
+    if (!keyed) {
         float bd[KNN];
         knn_sweep<KNN>(pos, lo, menv, mmax, slot, d.px, d.py, bd, bj);
     }
     float f[MLP_IN];
     (void)features(c, d, R, n, pos, vel, bj, 0.f, 0.f, 0.f, 0.f, 0.f, f);
-    float *x = g.X + (long long)di * MLP_IN;
+    // drone (lane / 4) + 16 i of the wave is stored by lanes 4 (lane / 4) .. + 3
+    int dst[4];
 #pragma unroll
-    for (int k = 0; k < MLP_IN; k += 4) *(float4 *)(x + k) = make_float4(f[k], f[k + 1], f[k + 2], f[k + 3]);
+    for (int i = 0; i < 4; ++i) dst[i] = __shfl(di, (lane >> 2) + 16 * i, 64);
+#pragma unroll
+    for (int k = 0; k < MLP_IN; k += 16) {
+#pragma unroll
+        for (int t = 0; t < 16; t += 4)
+            *(float4 *)(stage + lane * STAGE_ROW + t) = make_float4(f[k + t], f[k + t + 1], f[k + t + 2], f[k + t + 3]);
+        // the wave's own stage: its LDS operations complete in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 v = *(const float4 *)(stage + ((lane >> 2) + 16 * i) * STAGE_ROW + 4 * (lane & 3));
+            if (dst[i] >= 0) *(float4 *)(g.X + (long long)dst[i] * MLP_IN + k + 4 * (lane & 3)) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     float Fx, Fy, Fz;
     plain_aero(c, g.mask, d, R, n, T, pos, lo, menv, mmax, Fx, Fy, Fz);
+    if (!valid) return;
     float *y = g.Y + (long long)di * MLP_OUT;
     y[0] = R.r00 * Fx + R.r10 * Fy + R.r20 * Fz;
     y[1] = R.r01 * Fx + R.r11 * Fy + R.r21 * Fz;
@@ -856,7 +939,8 @@ hipError_t launch_sur_step(const SurArgs &sa, int act, int n_bins, int S, hipStr
 }
 
 hipError_t launch_datagen(const GenArgs &g, int n_bins, int S, hipStream_t st) {
-    hipLaunchKernelGGL(datagen_kernel, dim3(n_bins), dim3(S), sizeof(float4) * 4 * (size_t)S, st, g);
+    const size_t lds = sizeof(float4) * 3 * (size_t)S + sizeof(float) * STAGE_ROW * (size_t)S;  // 64 KB at 512 slots
+    hipLaunchKernelGGL(datagen_kernel, dim3(n_bins), dim3(S), lds, st, g);
     return hipGetLastError();
 }
 
