@@ -77,8 +77,8 @@ struct SurArgs {
     const float *norm;
     double *judge;
     float dz_ood;
-    float ood_speed, ood_rel;  // world speed / relative speed component bounds (0: off)
-    float near_dz, near_r2, far_dz;  // region fallback (near_dz 0: cylinder off; far_dz 0: off)
+    float ood_speed, ood_rel;  // world speed / relative speed component bounds (infinite: off)
+    float near_dz, near_r2, far_dz;  // region fallback (near_dz 0: cylinder off; far_dz infinite: off)
     float ood_tilt_s;          // sin^2(max tilt / 2) (0: off)
     int judge_mask;  // judge_stride - 1 (power of two), or -1 for no judging
     int knn_reuse;   // candidate lists (1) or every drone ranked every step (0)
@@ -220,14 +220,14 @@ __device__ __forceinline__ bool key_range(float px, float py) { return fabsf(px)
 // offsets from lo in ascending order, 2 per word; unused entries hold the
 // drone's own offset (never a member).  Ranking the list in slot order gives
 // exactly knn_sweep's result whenever every drone the sweep would pick is on
-// the list (the caller's margin test).
+// the list (the caller's margin test), the drone itself where it has -1.
 __device__ __forceinline__ void knn_list(const float4 *pos, int lo, int self, const uint32_t (&L)[6], float px,
                                          float py, int (&bj)[KNN]) {
     float bd[KNN];
 #pragma unroll
     for (int t = 0; t < KNN; ++t) {
         bd[t] = __builtin_inff();
-        bj[t] = -1;
+        bj[t] = self;  // missing
     }
 #pragma unroll
     for (int t = 0; t < LIST; ++t) {
@@ -261,19 +261,9 @@ __device__ __forceinline__ float wave_reduce(float x, Op op) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-// Raw surrogate inputs (see md.h): v_body, world up in the body frame, n/HOVER,
-// 8 x (dp, dv) of the nearest neighbours (world frame, zero if missing), z,
-// ground proximity (h_clip / max(z, h_clip))^2, 0-pad.
-// Returns whether a neighbour sits above within (0, dz_ood), inside the
-// cylinder |dz| < near_dz, dxy^2 < near_r2 (near_dz > 0), beyond |dz| >
-// far_dz (far_dz > 0), or (ood_rel > 0) moves relative to the drone faster
-// than ood_rel along an axis.  dz is the exact difference of the stored
-// heights and dxy^2 is formed as the neighbour ranking forms it, so the oracle
-// takes the same decisions.
-__device__ __forceinline__ bool features(const KConst &c, const Drone &d, const Rot &R, const float n[4],
-                                         const float4 *pos, const float4 *vel, const int bj[KNN],
-                                         float dz_ood, float ood_rel, float near_dz, float near_r2,
-                                         float far_dz, float f[MLP_IN]) {
+// The first raw surrogate inputs (see md.h): v_body, world up in the body frame,
+// n/HOVER.
+__device__ __forceinline__ void features_self(const KConst &c, const Drone &d, const Rot &R, const float n[4], float *f) {
     f[0] = R.r00 * d.vx + R.r10 * d.vy + R.r20 * d.vz;
     f[1] = R.r01 * d.vx + R.r11 * d.vy + R.r21 * d.vz;
     f[2] = R.r02 * d.vx + R.r12 * d.vy + R.r22 * d.vz;
@@ -282,37 +272,65 @@ __device__ __forceinline__ bool features(const KConst &c, const Drone &d, const 
     f[5] = R.r22;
 #pragma unroll
     for (int k = 0; k < 4; ++k) f[6 + k] = n[k] * c.hover_inv;
-    bool ood = false;
+}
+
+// The next 48: 8 x (dp, dv) of the nearest neighbours (world frame).  A
+// missing neighbour is the drone's own slot: its differences are exactly 0,
+// and no input needs a select or a branch.
+__device__ __forceinline__ void features_neighbours(const Drone &d, const float4 *pos, const float4 *vel,
+                                                    const int bj[KNN], float *f) {
 #pragma unroll
     for (int t = 0; t < KNN; ++t) {
-        const int j = bj[t];
-        float4 pj = make_float4(0.f, 0.f, 0.f, 0.f), vj = pj;
-        if (j >= 0) {
-            pj = pos[j];
-            vj = vel[j];
-        }
-        const bool h = j >= 0;
-        const float dz = pj.z - d.pz;
-        f[10 + 6 * t + 0] = h ? pj.x - d.px : 0.f;
-        f[10 + 6 * t + 1] = h ? pj.y - d.py : 0.f;
-        f[10 + 6 * t + 2] = h ? dz : 0.f;
-        f[10 + 6 * t + 3] = h ? vj.x - d.vx : 0.f;
-        f[10 + 6 * t + 4] = h ? vj.y - d.vy : 0.f;
-        f[10 + 6 * t + 5] = h ? vj.z - d.vz : 0.f;
-        ood |= h && dz > 0.f && dz < dz_ood;
-        const float d2 = knn_d2(pj, d.px, d.py);
-        ood |= h && near_dz > 0.f && fabsf(dz) < near_dz && d2 < near_r2;
-        ood |= h && far_dz > 0.f && fabsf(dz) > far_dz;
-        ood |= h && ood_rel > 0.f &&
-               (fabsf(f[10 + 6 * t + 3]) > ood_rel || fabsf(f[10 + 6 * t + 4]) > ood_rel ||
-                fabsf(f[10 + 6 * t + 5]) > ood_rel);
+        const float4 pj = pos[bj[t]], vj = vel[bj[t]];
+        f[6 * t + 0] = pj.x - d.px;
+        f[6 * t + 1] = pj.y - d.py;
+        f[6 * t + 2] = pj.z - d.pz;
+        f[6 * t + 3] = vj.x - d.vx;
+        f[6 * t + 4] = vj.y - d.vy;
+        f[6 * t + 5] = vj.z - d.vz;
     }
-    f[58] = d.pz;
+}
+
+// The last 6: z, ground proximity (h_clip / max(z, h_clip))^2, 0-pad.
+__device__ __forceinline__ void features_tail(const KConst &c, const Drone &d, float *f) {
+    f[0] = d.pz;
     const float gp = c.h_clip / fmaxf(d.pz, c.h_clip);
-    f[59] = gp * gp;
+    f[1] = gp * gp;
 #pragma unroll
-    for (int k = 60; k < MLP_IN; ++k) f[k] = 0.f;
-    return ood;
+    for (int k = 2; k < 6; ++k) f[k] = 0.f;
+}
+
+// Squared horizontal distance from its differences, formed as knn_d2 forms it.
+__device__ __forceinline__ float lateral_d2(float dx, float dy) {
+#pragma clang fp contract(off)
+    const float a = dx * dx, b = dy * dy;
+    return a + b;
+}
+
+__device__ __forceinline__ float max3f(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+// Whether a neighbour (differences f as from features_neighbours) sits above
+// within (0, dz_ood), inside the cylinder |dz| < near_dz, dxy^2 < near_r2,
+// beyond |dz| > far_dz, or moves relative to the drone faster than ood_rel
+// along an axis.  dz is the exact difference of the stored heights and dxy^2 is
+// formed as the neighbour ranking forms it, so the oracle takes the same
+// decisions.  Checks that are off have bounds that nothing passes (the host's
+// near_dz 0, far_dz and ood_rel infinite); a missing neighbour passes none but
+// the cylinder's, from which it is left out.
+__device__ __forceinline__ bool neighbours_ood(const float *f, const int bj[KNN], int self, float dz_ood, float ood_rel,
+                                               float near_dz, float near_r2, float far_dz) {
+    bool ood = false;
+    float rel = 0.f, far = 0.f;
+#pragma unroll
+    for (int t = 0; t < KNN; ++t) {
+        const float dz = f[6 * t + 2], adz = fabsf(dz);
+        ood |= (dz > 0.f) & (dz < dz_ood);
+        ood |= (adz < near_dz) & (lateral_d2(f[6 * t], f[6 * t + 1]) < near_r2) & (bj[t] != self);
+        rel = max3f(rel, fabsf(f[6 * t + 3]), fabsf(f[6 * t + 4]));
+        rel = max3f(rel, fabsf(f[6 * t + 5]), 0.f);
+        far = fmaxf(far, adz);
+    }
+    return ood | (rel > ood_rel) | (far > far_dz);
 }
 
 // Plain aerodynamic residual of the selected effects (world frame): ground
@@ -526,14 +544,15 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
     const KConst &c0 = a.c;
     const int S = blockDim.x;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    // LDS (248 bytes per slot: eight one-wave workgroups fit a CU's 160 KB,
-    // a 512-slot bin 124 KB)
+    // LDS (248 bytes per slot and 640 in all: eight one-wave workgroups fit a
+    // CU's 160 KB, a 512-slot bin 125 KB)
     float4 *posb = (float4 *)smem;              // [2][2S] positions, double buffered
     float4 *vel = posb + 4 * S;                 // [S] velocities (read before the step's second barrier)
     bf16 *feat = (bf16 *)(vel + S);             // [S][FEAT_STRIDE] network inputs; a row's first
                                                 // 24 bytes then take its outputs (OUT_ROW floats apart)
     uint2 *lst = (uint2 *)(feat + S * FEAT_STRIDE);   // [3][S] candidate lists, 12 16-bit slot offsets
     float *wred = (float *)(lst + 3 * S);             // [2][2][MAX_BIN_WAVES] per-wave max / min
+    float4 *xnorm = (float4 *)(wred + 4 * MAX_BIN_WAVES);  // input scales and offsets, in pairs
     const int slot = threadIdx.x, lane = threadIdx.x & 63, wbase = threadIdx.x & ~63;
     const int wave = threadIdx.x >> 6, n_waves = S >> 6;
     const int2 tab = a.bins.slot[blockIdx.x * S + slot];
@@ -543,6 +562,10 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
     const int mmax = a.bins.bin_mmax[blockIdx.x] & 0xffff;
     const int N = a.N;
     // device normalisation layout: x_inv_std[64], -x_mean * x_inv_std[64], y_mean[6], y_std[6]
+    // (the step's first barrier lies before the first read)
+    if (slot < MLP_IN / 2)
+        xnorm[slot] = make_float4(sa.norm[2 * slot], sa.norm[MLP_IN + 2 * slot], sa.norm[2 * slot + 1],
+                                  sa.norm[MLP_IN + 2 * slot + 1]);
 
     Drone d{};
     d.qw = 1.f;
@@ -632,12 +655,14 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
         if (!use_list) {
             float bd[KNN];
             knn_sweep<KNN>(pos, lo, menv, mmax, slot, d.px, d.py, bd, bj);
+#pragma unroll
+            for (int t = 0; t < KNN; ++t) bj[t] = bj[t] >= 0 ? bj[t] : slot;
         } else if (rebuild) {
             float bd[LIST];
             int bl[LIST];
             knn_sweep<LIST>(pos, lo, menv, mmax, slot, d.px, d.py, bd, bl);
 #pragma unroll
-            for (int t = 0; t < KNN; ++t) bj[t] = bl[t];
+            for (int t = 0; t < KNN; ++t) bj[t] = bl[t] >= 0 ? bl[t] : slot;
             // the list in slot order: every candidate at or before the LIST-th
             // in (distance, slot) order, found by a second pass
             const float r2 = bd[LIST - 1];
@@ -681,29 +706,39 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
         nfull += (valid && rebuild) ? 1 : 0;
         // ---- features -> standardised bfloat16 row
         bool ood;
-        float f[MLP_IN];
         {
-            const Rot R = rot_of(d);
-            ood = features(c, d, R, n, pos, vel, bj, sa.dz_ood, sa.ood_rel, sa.near_dz, sa.near_r2, sa.far_dz, f);
-        }
-        // outside the trained region: fast or tilted drones take the plain terms
-        ood |= sa.ood_speed > 0.f &&
-               (fabsf(d.vx) > sa.ood_speed || fabsf(d.vy) > sa.ood_speed || fabsf(d.vz) > sa.ood_speed);
-        ood |= sa.ood_tilt_s > 0.f && tilt_sq(d) > sa.ood_tilt_s;
-        ood = ood && valid;
-        bf16 *row = feat + slot * FEAT_STRIDE;
-        // the normalisation is read here each step rather than held in
-        // scalar registers for the launch (the empty asm keeps the loads in
-        // the loop), which leaves the scalar registers to the step's constants
-        const float *nrm = sa.norm;
-        asm volatile("" : "+s"(nrm));
+            float f[MLP_IN];
+            {
+                const Rot R = rot_of(d);
+                features_self(c, d, R, n, f);
+            }
+            // (one block: with a branch per missing neighbour and idle lane, and
+            // the scales behind a generic pointer, the rows were written
+            // through a hundred small blocks, each waiting for its own loads:
+            // 680 against 579 us, 4096 x 32 drones, 20 steps)
+            features_neighbours(d, pos, vel, bj, f + 10);
+            ood = neighbours_ood(f + 10, bj, slot, sa.dz_ood, sa.ood_rel, sa.near_dz, sa.near_r2, sa.far_dz);
+            // outside the trained region: fast or tilted drones take the plain terms
+            ood |= max3f(fabsf(d.vx), fabsf(d.vy), fabsf(d.vz)) > sa.ood_speed;
+            ood |= (sa.ood_tilt_s > 0.f) & (tilt_sq(d) > sa.ood_tilt_s);
+            // decided here: put off to its use, its operands would be held
+            // across the network
+            unsigned decided = (ood & valid) ? 1u : 0u;
+            asm volatile("" : "+v"(decided));
+            ood = decided != 0u;
+            features_tail(c, d, f + 58);
+            bf16 *row = feat + slot * FEAT_STRIDE;
 #pragma unroll
-        for (int k = 0; k < MLP_IN; k += 8) {
-            bf16x8 v;
+            for (int k = 0; k < MLP_IN; k += 8) {
+                bf16x8 v;
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-                v[t] = valid ? (bf16)fmaf(f[k + t], nrm[k + t], nrm[MLP_IN + k + t]) : (bf16)0.f;
-            *(bf16x8 *)(row + k) = v;
+                for (int t = 0; t < 8; t += 2) {
+                    const float4 m = xnorm[(k + t) / 2];  // scale, offset of two inputs
+                    v[t] = (bf16)fmaf(f[k + t], m.x, m.y);
+                    v[t + 1] = (bf16)fmaf(f[k + t + 1], m.z, m.w);
+                }
+                *(bf16x8 *)(row + k) = v;
+            }
         }
         __syncthreads();
         mlp_wave(feat + wbase * FEAT_STRIDE, (float *)(feat + wbase * FEAT_STRIDE), sa.W, sa.b, lane);
@@ -719,7 +754,7 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
         float y[MLP_OUT];
 #pragma unroll
         for (int o = 0; o < MLP_OUT; ++o)
-            y[o] = ((const float *)feat)[slot * OUT_ROW + o] * nrm[2 * MLP_IN + MLP_OUT + o] + nrm[2 * MLP_IN + o];
+            y[o] = ((const float *)feat)[slot * OUT_ROW + o] * sa.norm[2 * MLP_IN + MLP_OUT + o] + sa.norm[2 * MLP_IN + o];
         float Fx = R.r02 * T, Fy = R.r12 * T, Fz = R.r22 * T - c.mg;
         float ax, ay, az;
         // surrogate force, body -> world
@@ -870,7 +905,12 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
         knn_sweep<KNN>(pos, lo, menv, mmax, slot, d.px, d.py, bd, bj);
     }
     float f[MLP_IN];
-    (void)features(c, d, R, n, pos, vel, bj, 0.f, 0.f, 0.f, 0.f, 0.f, f);
+    int nj[KNN];
+#pragma unroll
+    for (int t = 0; t < KNN; ++t) nj[t] = bj[t] >= 0 ? bj[t] : slot;
+    features_self(c, d, R, n, f);
+    features_neighbours(d, pos, vel, nj, f + 10);
+    features_tail(c, d, f + 58);
     // drone (lane / 4) + 16 i of the wave is stored by lanes 4 (lane / 4) .. + 3
     int dst[4];
 #pragma unroll
@@ -912,7 +952,7 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
 
 size_t sur_lds_bytes(int S) {
     return sizeof(float4) * 5 * (size_t)S + sizeof(bf16) * (size_t)S * FEAT_STRIDE + sizeof(uint2) * 3 * (size_t)S +
-           sizeof(float) * 4 * MAX_BIN_WAVES;
+           sizeof(float) * 4 * MAX_BIN_WAVES + sizeof(float4) * (MLP_IN / 2);
 }
 
 template <int ACT>
@@ -1077,11 +1117,12 @@ md_status surrogate_step(md_ctx *ctx, const md_state *s, const float *d_action, 
     sa.norm = ctx->sur->norm;
     sa.judge = ctx->sur->judge;
     sa.dz_ood = ctx->sur->dz_ood;
-    sa.ood_speed = ctx->sur->ood_speed;
-    sa.ood_rel = ctx->sur->ood_rel;
+    auto bound = [](float x) { return x > 0.f ? x : INFINITY; };  // 0: off
+    sa.ood_speed = bound(ctx->sur->ood_speed);
+    sa.ood_rel = bound(ctx->sur->ood_rel);
     sa.near_dz = ctx->sur->near_dz;
     sa.near_r2 = ctx->sur->near_r2;
-    sa.far_dz = ctx->sur->far_dz;
+    sa.far_dz = bound(ctx->sur->far_dz);
     sa.ood_tilt_s = ctx->sur->ood_tilt_s;
     sa.judge_mask = ctx->sur->judge_stride > 0 ? ctx->sur->judge_stride - 1 : -1;
     sa.knn_reuse = ctx->sur->knn_reuse ? 1 : 0;
