@@ -72,6 +72,10 @@ __device__ __forceinline__ void dr_constants(const KConst &c, const DrPtr &dr, i
     for (int k = 0; k < 4; ++k) bias[k] = dr.scale[(MD_DR_BIAS + k) * N + di];
 }
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);  // one instruction; the compiler forms two
+}
+
 // Philox4x32-10 (Salmon et al., SC 2011): ten rounds of the two 32x32-bit
 // products with the round multipliers, high halves xored with the other
 // counter words and the round key, key bumped by the Weyl constants.  Each
@@ -84,7 +88,7 @@ __device__ __forceinline__ uint4 philox4x32(uint4 c, uint32_t k0, uint32_t k1) {
         const unsigned long long p1 = (unsigned long long)0xCD9E8D57u * c.z;
         const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
         const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        c = make_uint4(hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0);
+        c = make_uint4(xor3(hi1, c.y, k0), lo1, xor3(hi0, c.w, k1), lo0);
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -524,7 +528,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
                 __syncthreads();
                 acc = dw_block_rest(sums, slots, slot, menv, acc);
             } else {
-                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM>(
+                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, true, DIST != 0>(
                     c, buf, tmat, a.tstride, slots, slot, sub, lo, mmax, menv, uniform, d, dense);
             }
             Fz -= cl.K1 * acc;

@@ -154,6 +154,57 @@ __device__ __forceinline__ float dw_lanes(const KConst &c0, const float4 *buf, i
     return acc;
 }
 
+// The one-lane sweep's sum, bit for bit, by tests first: 32 candidates' signs
+// (partner above, and a margin that may give a term) into a word per lane,
+// then each lane's set bits in ascending order.  `dense` as in
+// dw_pairs_rot_sparse.  The gather of the set bits is a serial chain through
+// LDS, so it pays where the step around it keeps the vector ALU busy and not
+// where the sweep alone is the step (SCAN, see dw_sum).
+template <bool DZMIN>
+__device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 *buf, int slots, int lo, int mmax,
+                                                 int menv, const Drone &d, int &dense) {
+    float acc = 0.f;
+    int rounds = 0;
+#pragma unroll 1
+    for (int j0 = 0; j0 < mmax; j0 += 32) {
+        uint32_t bits = 0;
+        const int n = min(32, (mmax - j0 + 7) & ~7);
+        {
+            const KConst c = margin_consts(c0);
+            // (candidates past the environment are read from the rest of the
+            // buffer, which holds 2 slots entries, and masked below)
+#pragma unroll 1
+            for (int k = 0; k < n; k += 8) {
+                float x[8];
+                const float4 *q = buf + min(lo + j0 + k, 2 * slots - 8);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float4 p = q[u];
+                    const float below = d.pz - p.z;  // its sign: the partner is above
+                    const float m = dw_margin<DZMIN>(c, p.x - d.px, p.y - d.py, fabsf(below));
+                    x[u] = __uint_as_float(__float_as_uint(m) & __float_as_uint(below));
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) bits = push_sign(bits, x[u]);
+            }
+        }
+        bits <<= 32 - n;  // candidate j0 + k in bit 31 - k
+        const int left = menv - j0;
+        bits &= left >= 32 ? ~0u : ~(~0u >> max(left, 0));
+        const KConst c = pair_consts(c0);
+        while (__ballot(bits != 0u) != 0ull) {
+            const int k = bits != 0u ? __builtin_clz(bits) : 0;
+            const float4 p = buf[lo + j0 + k];
+            const float t = dw_term<DZMIN>(c, p.x - d.px, p.y - d.py, p.z - d.pz);
+            acc += bits != 0u ? t : 0.f;
+            bits &= ~(0x80000000u >> k);
+            ++rounds;
+        }
+    }
+    dense = 5 * rounds > 2 * mmax ? SPARSE_RETRY - 1 : 0;
+    return acc;
+}
+
 // Pair-symmetric downwash sweep: each unordered pair of an environment is
 // evaluated once, by lane i for partners (i + d) mod M, d = 1..(M-1)/2, plus
 // d = M/2 from the lower half when M is even.  The term goes to the lower
@@ -567,7 +618,10 @@ __device__ __forceinline__ float dw_block_rest(const float *sums, int slots, int
 // sweep through wave shuffles (environments inside one wave); SYM 3: the same
 // sweep as a whole-wave rotation on interleaved uniform bins (bitwise equal
 // to SYM 2).
-template <int LPD, int UNROLL, int SYM, bool TESTS = true>
+// SCAN: the one-lane sweep by tests first, in the kernels with wind or
+// randomisation, whose other work covers its latencies (4096 x 32 randomised
+// drones, 50 steps: 367 without, 346 us with it; the plain step 299 and 319).
+template <int LPD, int UNROLL, int SYM, bool TESTS = true, bool SCAN = false>
 __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, float *tmat, int ts, int slots, int slot,
                                         int sub, int lo, int mmax, int menv, bool uniform, const Drone &d,
                                         int &dense) {
@@ -607,9 +661,14 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
             acc += t.z;
             acc += t.w;
         }
+    } else if (SCAN && LPD == 1 && mmax >= SPARSE_MIN_ENV && (dense = __builtin_amdgcn_readfirstlane(dense)) == 0) {
+        acc = c.dz_min > 0.f ? dw_sweep_sparse<true>(c, buf, slots, lo, mmax, menv, d, dense)
+                             : dw_sweep_sparse<false>(c, buf, slots, lo, mmax, menv, d, dense);
     } else if (c.dz_min > 0.f) {
+        dense -= SCAN && dense > 0 ? 1 : 0;
         acc = dw_sweep<true, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     } else {
+        dense -= SCAN && dense > 0 ? 1 : 0;
         acc = dw_sweep<false, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     }
     // the partial sums of a drone's lanes, combined across the lanes of a

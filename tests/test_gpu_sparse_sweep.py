@@ -66,3 +66,30 @@ def test_block_sweep_per_step(scale):
             pu.assert_blocks(g.snapshot(), ref, what="scale %g step %d" % (scale, k))
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("scale", [1.0, 0.4, 0.05])
+@pytest.mark.parametrize("kind", ["wind", "randomized"])
+@pytest.mark.parametrize("layout", ["uniform32", "ragged64"])
+def test_one_lane_sweep_equals_matrix_sweep(layout, kind, scale):
+    """The one-lane sweep of the kernels with wind or randomisation against
+    the LDS-matrix sweep, which evaluates every pair and sums in the same
+    order."""
+    if layout == "uniform32":
+        w = _packed(23, (4, 4, 2), scale, 10)
+    else:
+        w = wl.thin_envs(_packed(31, (8, 4, 2), scale, 11), 12, m_lo=1)
+    if kind == "wind":
+        w["wind"] = wl.dr_wind(w, 3)
+    else:
+        w = dict(w, dr=wl.domain_randomization(w, 4), wind=wl.dr_wind(w, 5))
+    got = []
+    for sym in (1, 0):
+        print("%s %s scale %g sweep %d" % (layout, kind, scale, sym), flush=True)
+        g = pu.DeviceRun(w, cfg=dict(lanes_per_drone=1, unroll=4, waves_per_group=2, pair_symmetric=sym))
+        obs = g.run(21, obs_slots=21)
+        got.append((g.snapshot(), obs))
+        g.close()
+    np.testing.assert_array_equal(got[1][1], got[0][1])
+    for k in ("p", "q", "v", "w", "rpm", "pid_int", "wind"):
+        np.testing.assert_array_equal(got[1][0][k], got[0][0][k])
