@@ -7,6 +7,7 @@ library is missing this module raises on first use -- there is no fallback.
 import ctypes
 import os
 import re
+import struct
 
 import numpy as np
 
@@ -106,7 +107,7 @@ def lib():
         "md_last_error": (ctypes.c_char_p, [_VP]),
         "md_bind_layout": (ctypes.c_int32, [_VP, ctypes.POINTER(ctypes.c_int32), ctypes.c_int,
                                             ctypes.c_int]),
-        "md_step": (ctypes.c_int32, [_VP, ctypes.POINTER(md_state), _VP, ctypes.c_int, _VP,
+        "md_step": (ctypes.c_int32, [_VP, _VP, _VP, ctypes.c_int, _VP,
                                      ctypes.c_int, ctypes.c_int, ctypes.c_int64, _VP]),
     }
     for name, (res, args) in sig.items():
@@ -140,13 +141,33 @@ def check(status, ctx=None):
         raise MdError(status, msg)
 
 
+_current_raw_stream = None  # torch's current stream of the current device, as an address
+
+
 def _stream_ptr(stream):
+    # every call that steps, predicts or trains passes here: torch's own
+    # Stream object costs more than the launch it would be used for
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        global _current_raw_stream
+        if _current_raw_stream is None:
+            import torch
+            torch.cuda.init()
+            raw, dev = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+            _current_raw_stream = lambda: raw(dev())  # noqa: E731
+        return _current_raw_stream()
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
+
+
+_STATE_PTRS = struct.Struct("%dQ" % len(md_state._fields_))
+
+
+def _state_arg(state):
+    """What the C ABI takes for `const md_state *`: the packed pointers of a
+    DeviceState, or a reference to an md_state."""
+    return state.pointers() if hasattr(state, "pointers") else ctypes.byref(
+        state.as_md_state() if hasattr(state, "as_md_state") else state)
 
 
 # ------------------------------------------------------------------ C ABI
@@ -193,14 +214,17 @@ def md_bind_layout(ctx, env_offsets):
 def md_step(ctx, state, action, action_per_step, obs=None, n_obs_slots=0, n_steps=1, step0=0,
             stream=None):
     """state: DeviceState (or md_state); action/obs: CUDA float32 tensors."""
-    ms = state.as_md_state() if hasattr(state, "as_md_state") else state
-    st = lib().md_step(ctx, ctypes.byref(ms), _VP(action.data_ptr()), int(bool(action_per_step)),
-                       _VP(obs.data_ptr()) if obs is not None else None, int(n_obs_slots),
+    st = lib().md_step(ctx, _state_arg(state), action.data_ptr(), 1 if action_per_step else 0,
+                       None if obs is None else obs.data_ptr(), int(n_obs_slots),
                        int(n_steps), int(step0), _stream_ptr(stream))
-    check(st, ctx)
+    if st != MD_OK:
+        check(st, ctx)
 
 
 # ------------------------------------------------------------------ device buffers
+
+_STATE_KEYS = tuple(n for n, _ in md_state._fields_)
+
 
 class DeviceState:
     """Float32 SoA state on the GPU, one torch tensor [rows][N] per field."""
@@ -260,9 +284,12 @@ class DeviceState:
         return d
 
     def as_md_state(self):
-        return md_state(*[self.t[k].data_ptr() if k in self.t else None
-                          for k in ("p", "q", "v", "w", "pid_int", "rpm", "ctl", "rpm_cmd", "act_hist",
-                                    "act_count", "wind", "obs_hist", "obs_count")])
+        return md_state.from_buffer_copy(self.pointers())
+
+    def pointers(self):
+        """The bytes of as_md_state(): the blocks' addresses as they are now."""
+        t = self.t
+        return _STATE_PTRS.pack(*[t[k].data_ptr() if k in t else 0 for k in _STATE_KEYS])
 
 
 # ------------------------------------------------------------------ surrogate network
@@ -318,10 +345,10 @@ def md_mlp_get_norm(m):
 
 
 def md_mlp_forward(m, X, B=None, Y=None, stream=None):
-    B = X.shape[0] if B is None else B
-    mlp_check(lib().md_mlp_forward(m, _VP(X.data_ptr()), int(B),
-                                   _VP(Y.data_ptr()) if Y is not None else None,
-                                   _stream_ptr(stream)), m)
+    B = X.shape[0] if B is None else int(B)
+    st = lib().md_mlp_forward(m, X.data_ptr(), B, None if Y is None else Y.data_ptr(), _stream_ptr(stream))
+    if st != MD_OK:
+        mlp_check(st, m)
 
 
 MD_MLP_NOALLOC_MAX_BATCH = 4096
@@ -330,14 +357,17 @@ MD_MLP_NOALLOC_MAX_BATCH = 4096
 def md_mlp_forward_noalloc(m, X, Y, B=None, stream=None):
     """md_mlp_forward with its intermediates on chip (allocates nothing, keeps
     nothing); Y [B][6] float32 receives the outputs."""
-    B = X.shape[0] if B is None else B
-    mlp_check(lib().md_mlp_forward_noalloc(m, _VP(X.data_ptr()), int(B), _VP(Y.data_ptr()),
-                                           _stream_ptr(stream)), m)
+    B = X.shape[0] if B is None else int(B)
+    st = lib().md_mlp_forward_noalloc(m, X.data_ptr(), B, Y.data_ptr(), _stream_ptr(stream))
+    if st != MD_OK:
+        mlp_check(st, m)
 
 
 def md_mlp_backward(m, T, B=None, stream=None):
-    B = T.shape[0] if B is None else B
-    mlp_check(lib().md_mlp_backward(m, _VP(T.data_ptr()), int(B), _stream_ptr(stream)), m)
+    B = T.shape[0] if B is None else int(B)
+    st = lib().md_mlp_backward(m, T.data_ptr(), B, _stream_ptr(stream))
+    if st != MD_OK:
+        mlp_check(st, m)
 
 
 def md_mlp_get_grads(m):

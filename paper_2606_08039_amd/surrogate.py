@@ -138,9 +138,12 @@ def predict(m, X, batch=None):
     import torch
     B = batch or 4096
     Y = torch.empty((X.shape[0], 6), dtype=torch.float32, device=X.device)
-    for o in range(0, X.shape[0], B):
-        nb = min(B, X.shape[0] - o)
-        md.md_mlp_forward(m, X[o:o + nb], nb, Y[o:o + nb])
+    # addresses of the batches' first rows, without a tensor for each
+    n, x, y = X.shape[0], X.data_ptr(), Y.data_ptr()
+    x_row, y_row = 4 * X.stride(0), 4 * Y.stride(0)
+    forward, stream = md.lib().md_mlp_forward, md._stream_ptr(None)
+    for o in range(0, n, B):
+        md.mlp_check(forward(m, x + o * x_row, min(B, n - o), y + o * y_row, stream), m)
     torch.cuda.synchronize()
     return Y
 
