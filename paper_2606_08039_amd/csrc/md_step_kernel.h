@@ -411,6 +411,9 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
     float nprev[4] = {0.f, 0.f, 0.f, 0.f};
     float rpy[3] = {0.f, 0.f, 0.f};  // the previous row's angles
     int pslot = 0;
+    constexpr bool held_motor = DIST != 2 && ACT >= 1;
+    bool motor_due = true;  // uniform
+    float T = 0.f, tx = 0.f, ty = 0.f, tz = 0.f;
     int dense = 0;  // steps to sweep without tests (see the sparse sweeps)
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
@@ -455,6 +458,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
                     else
                         control<ACT>(c, d, cmd, I, sp, n);
                 }
+                motor_due = step == 0 || phase == 0;
                 phase = (phase + 1 == c.decim) ? 0 : phase + 1;
             }
         } else {
@@ -489,9 +493,9 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
             }
             hslot = (hslot + 1 == MD_DR_HIST) ? 0 : hslot + 1;
         }
-        // ---- motor model and mixer (Eq. 1-3)
-        float T, tx, ty, tz;
-        motor(cl, n, T, tx, ty, tz);
+        // ---- motor model and mixer (Eq. 1-3), when the rotor speeds changed:
+        // between controller updates they are held
+        if (!held_motor || motor_due) motor(cl, n, T, tx, ty, tz);
         const Rot R = rot_of(d);
         float Fx = R.r02 * T, Fy = R.r12 * T, Fz = R.r22 * T - cl.mg;
         // ---- ground effect (Eq. 4)
