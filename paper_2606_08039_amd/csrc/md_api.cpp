@@ -64,6 +64,7 @@ KConst make_kconst(const md_params &p, const md_derived &d, double dt, int decim
     c.C3s = (float)(std::sqrt(2.0 * std::log(2.0)) * p.C3);
     c.C2c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C2);
     c.C3c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C3);
+    c.reach = (float)((std::sqrt(320.0 * std::log(2.0)) * std::fabs(p.C2) + 1.0) * 2.0 * MEMO_MOVE * 1.001);
     for (int k = 0; k < 3; ++k) {
         c.pkp[k] = (float)p.pos_kp[k];
         c.pki[k] = (float)p.pos_ki[k];

@@ -351,10 +351,14 @@ __device__ __forceinline__ bool dw_near(float d2) { return d2 < 100.f; }
 // then keeps above -160.  Where it is not negative, the exponent lies below
 // -159 (a few roundings), 2^x is 0 (the smallest denormal is 2^-149) and so is
 // the term.  A NaN position passes or not; its terms are gated to 0 anyway.
-template <bool DZMIN>
+// KEPT: the radius is widened by `reach`, so that the outcome holds for the
+// pair as long as neither drone has moved MEMO_MOVE: the offset changes by at
+// most 2 MEMO_MOVE, the radius sqrt(160) beta' by C2c times that.
+template <bool DZMIN, bool KEPT>
 __device__ __forceinline__ float dw_margin(const KConst &c, float dx, float dy, float adz) {
     const float dze = DZMIN ? fmaxf(adz, c.dz_min) : adz;
-    const float bc = fmaf(c.C2c, dze, c.C3c);
+    float bc = fmaf(c.C2c, dze, c.C3c);
+    if (KEPT) bc = fabsf(bc) + c.reach;
     return fmaf(-bc, bc, fmaf(dx, dx, fmaf(dy, dy, -1.6e-28f)));
 }
 

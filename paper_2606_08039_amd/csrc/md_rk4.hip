@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
         for (int k = 0; k < 4; ++k) sp[k] = a.s.ctl[k * N + di];
     int phase = (ACT >= 1) ? (int)(a.step0 % (long long)c.decim) : 0;
     int oslot = 0;
-    int dense = 0;  // sweeps (stages) to run without tests (see the sparse sweeps)
+    SweepMemo memo;
     const float half_dt = 0.5f * c.dt, sixth_dt = c.dt * (1.f / 6.f);
     for (int step = 0; step < a.n_steps; ++step) {
         // ---- rotor speeds, held over the step
@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
                     // one buffer: the barrier after the sweep ends its reads
                     const int lane = slot & 63;
                     float4 *own = lds_pos + 2 * (slot - lane) + lane;
-                    own[0] = own[64] = make_float4(d.px, d.py, d.pz, 0.f);
+                    own[0] = own[64] = make_float4(d.px, d.py, d.pz, dw_block_asks(memo, valid, d));
                 } else if (SYM == 3) {
                     // interleaved uniform bins: each wave's positions twice (128 entries)
                     const int lane = slot & 63;
@@ -143,8 +143,8 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
             if (MASK & 4u) {
                 if (block) {
                     float *sums = (float *)(lds_pos + 2 * slots);
-                    const float part = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d, dense)
-                                                      : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d, dense);
+                    const float part = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, valid, d, memo)
+                                                      : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, valid, d, memo);
                     __syncthreads();
                     Fz -= c.K1 * dw_block_rest(sums, slots, slot, menv, part);
                 } else {
@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
                     // places than around the permute sweep, and the two are
                     // to round alike (453 against 470 us, 4096 x 32 drones)
                     Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, false>(
-                                     c, buf, tmat, a.tstride, slots, slot, 0, lo, mmax, menv, uniform, d, dense);
+                                     c, buf, tmat, a.tstride, slots, slot, 0, lo, mmax, menv, uniform, valid, d, memo);
                 }
             }
             // time derivative k of the stage

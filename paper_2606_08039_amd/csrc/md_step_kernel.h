@@ -414,7 +414,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
     constexpr bool held_motor = DIST != 2 && ACT >= 1;
     bool motor_due = true;  // uniform
     float T = 0.f, tx = 0.f, ty = 0.f, tz = 0.f;
-    int dense = 0;  // steps to sweep without tests (see the sparse sweeps)
+    SweepMemo memo;
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
         if (MASK & 4u) {
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
                 // one buffer: the barrier after the sweep ends its reads
                 const int lane = slot & 63;
                 float4 *own = lds_pos + 2 * (slot - lane) + lane;
-                own[0] = own[64] = make_float4(d.px, d.py, d.pz, 0.f);
+                own[0] = own[64] = make_float4(d.px, d.py, d.pz, dw_block_asks(memo, valid, d));
             } else if (SYM == 3) {
                 // interleaved uniform bins: each wave's positions twice (128 entries)
                 const int lane = slot & 63;
@@ -520,20 +520,20 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
                                      writer ? di * 4 : 20 * N * 4, N * 4,
                                      {d.px, d.py, d.pz, d.qw, d.qx, d.qy, d.qz, rpy[0], rpy[1], rpy[2],
                                       d.vx, d.vy, d.vz, d.wx, d.wy, d.wz, nprev[0], nprev[1], nprev[2], nprev[3]}};
-                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d, dense, seg)
-                                         : dw_rot<false>(c, own, lane, mmax, d, dense, seg);
+                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, valid, d, memo, seg)
+                                         : dw_rot<false>(c, own, lane, mmax, valid, d, memo, seg);
                 } else {
-                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, d, dense) : dw_rot<false>(c, own, lane, mmax, d, dense);
+                    acc = c.dz_min > 0.f ? dw_rot<true>(c, own, lane, mmax, valid, d, memo) : dw_rot<false>(c, own, lane, mmax, valid, d, memo);
                 }
             } else if (block) {
                 float *sums = (float *)(lds_pos + 2 * slots);
-                acc = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, d, dense)
-                                     : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, d, dense);
+                acc = c.dz_min > 0.f ? dw_block<true>(c, lds_pos, sums, slots, slot, lo, menv, valid, d, memo)
+                                     : dw_block<false>(c, lds_pos, sums, slots, slot, lo, menv, valid, d, memo);
                 __syncthreads();
                 acc = dw_block_rest(sums, slots, slot, menv, acc);
             } else {
-                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, true, DIST != 0>(
-                    c, buf, tmat, a.tstride, slots, slot, sub, lo, mmax, menv, uniform, d, dense);
+                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, true, DIST>(
+                    c, buf, tmat, a.tstride, slots, slot, sub, lo, mmax, menv, uniform, valid, d, memo);
             }
             Fz -= cl.K1 * acc;
         }

@@ -42,11 +42,39 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // steps, block sweep 617 -> 395 us; 4096 x 64, 60 steps, rotation sweep with
 // observations 433 -> 325 us, without 377 -> 240 us; 8192 x 32, 60 steps with
 // observations 300 -> 284 us.
+// The outcomes outlast a step: the block sweep, the rotation of 64 drones and
+// the one-lane sweep of the randomised step keep them until a drone of the
+// environment (or of the wave) has moved MEMO_MOVE, with a radius that allows
+// for it, and evaluate a few pairs more instead of testing all.  A pair that
+// is evaluated needlessly adds its exact 0.  Formed at every step -> kept: 512
+// x 256 drones, 50 steps 394 -> 175 us, Runge-Kutta 256 x 256, 20 steps 572 ->
+// 258 us; 2048 x 64, 60 steps with observations 200 -> 167 us, without 178 ->
+// 140 us; 4096 x 32 randomised, 50 steps 333 -> 312 us.
 constexpr int SPARSE_RETRY = 8;
 // Smallest environment that takes tests: at 32 drones a third of the 16 shifts
 // is needed by some lane and the tests pay a little; at 16 they do not (223
 // without, 226 us with them, 8192 environments, 100 steps with observations).
 constexpr int SPARSE_MIN_ENV = 32;
+
+// What a sweep keeps from step to step: where the drone stood at the last
+// tests, their outcome (a uniform word of shifts; in the block sweep word k in
+// lane k; in the one-lane sweep a word of candidates per lane), and the steps
+// to run without tests.
+struct SweepMemo {
+    float x = __builtin_nanf(""), y = 0.f, z = 0.f;  // (x a NaN: nothing is kept)
+    uint32_t need = 0;
+    int dense = 0;  // (uniform)
+    __device__ __forceinline__ bool moved(const Drone &d) const {  // (a NaN has moved)
+        const float ex = d.px - x, ey = d.py - y, ez = d.pz - z;
+        return !(ex * ex + ey * ey + ez * ez < MEMO_MOVE * MEMO_MOVE);
+    }
+    __device__ __forceinline__ void stand(const Drone &d) {
+        x = d.px;
+        y = d.py;
+        z = d.pz;
+    }
+    __device__ __forceinline__ void forget() { x = __builtin_nanf(""); }
+};
 
 __device__ __forceinline__ uint32_t push_sign(uint32_t bits, float x) {
     return __builtin_amdgcn_alignbit(bits, __float_as_uint(x), 31);  // bits << 1 | sign
@@ -156,20 +184,26 @@ __device__ __forceinline__ float dw_lanes(const KConst &c0, const float4 *buf, i
 
 // The one-lane sweep's sum, bit for bit, by tests first: 32 candidates' signs
 // (partner above, and a margin that may give a term) into a word per lane,
-// then each lane's set bits in ascending order.  `dense` as in
-// dw_pairs_rot_sparse.  The gather of the set bits is a serial chain through
+// then each lane's set bits in ascending order.  KEEP: the outcomes are kept
+// (also of partners that may come to be above).  The gather of the set bits is a serial chain through
 // LDS, so it pays where the step around it keeps the vector ALU busy and not
 // where the sweep alone is the step (SCAN, see dw_sum).
-template <bool DZMIN>
-__device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 *buf, int slots, int lo, int mmax,
-                                                 int menv, const Drone &d, int &dense) {
+template <bool DZMIN, bool KEEP>
+__device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 *buf, int slots, int slot, int lo,
+                                                 int mmax, int menv, const Drone &d, SweepMemo &memo) {
     float acc = 0.f;
     int rounds = 0;
+    // outcomes are kept where one word and one wave hold them all
+    const bool keep = KEEP && mmax <= 32 && slots == 64;
+    const float lift = KEEP ? 2.002f * MEMO_MOVE : 0.f;
+    const bool test = !keep || __ballot(menv > 0 && memo.moved(d)) != 0ull;
+    if (test && keep) memo.stand(d);
 #pragma unroll 1
     for (int j0 = 0; j0 < mmax; j0 += 32) {
-        uint32_t bits = 0;
-        const int n = min(32, (mmax - j0 + 7) & ~7);
-        {
+        uint32_t bits = memo.need;
+        if (test) {
+            bits = 0;
+            const int n = min(32, (mmax - j0 + 7) & ~7);
             const KConst c = margin_consts(c0);
             // (candidates past the environment are read from the rest of the
             // buffer, which holds 2 slots entries, and masked below)
@@ -180,17 +214,20 @@ __device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const float4 p = q[u];
-                    const float below = d.pz - p.z;  // its sign: the partner is above
-                    const float m = dw_margin<DZMIN>(c, p.x - d.px, p.y - d.py, fabsf(below));
-                    x[u] = __uint_as_float(__float_as_uint(m) & __float_as_uint(below));
+                    // negative: the partner is above, or may come to be
+                    const float below = d.pz - p.z;
+                    const float m = dw_margin<DZMIN, KEEP>(c, p.x - d.px, p.y - d.py, fabsf(below));
+                    x[u] = __uint_as_float(__float_as_uint(m) & __float_as_uint(below - lift));
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) bits = push_sign(bits, x[u]);
             }
+            bits <<= 32 - n;  // candidate j0 + k in bit 31 - k
+            const int left = menv - j0;
+            bits &= left >= 32 ? ~0u : ~(~0u >> max(left, 0));
+            if (keep) bits &= ~(0x80000000u >> ((slot - lo) & 31));  // not itself
+            memo.need = bits;
         }
-        bits <<= 32 - n;  // candidate j0 + k in bit 31 - k
-        const int left = menv - j0;
-        bits &= left >= 32 ? ~0u : ~(~0u >> max(left, 0));
         const KConst c = pair_consts(c0);
         while (__ballot(bits != 0u) != 0ull) {
             const int k = bits != 0u ? __builtin_clz(bits) : 0;
@@ -201,7 +238,10 @@ __device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 
             ++rounds;
         }
     }
-    dense = 5 * rounds > 2 * mmax ? SPARSE_RETRY - 1 : 0;
+    if (5 * rounds > 2 * mmax) {
+        memo.dense = SPARSE_RETRY - 1;
+        memo.forget();
+    }
     return acc;
 }
 
@@ -356,31 +396,42 @@ __device__ __forceinline__ float dw_pairs_rot(const KConst &c0, const float4 *ow
     return acc;
 }
 
-// The same sum, bit for bit, by tests first: every shift's margin, then the
-// shifts that some lane of the wave needs, ascending.  `dense` counts down the
-// steps to run without the tests (uniform in the wave).
+// The same sum, bit for bit, from the shifts that some lane of the wave needs,
+// ascending.  With 64 drones the outcomes are kept until a drone has moved;
+// with 32 the tests are run at every step: sixteen cost no more than keeping
+// their outcomes (8192 x 32 drones, 60 steps with observations: 276 us run,
+// 284-300 us kept; 2048 x 64 178 run, 139 us kept).
 template <bool DZMIN, int E, class Seg>
-__device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const float4 *own, int lane, const Drone &d,
-                                                     const Seg &seg, int &dense) {
+__device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const float4 *own, int lane, bool valid,
+                                                     const Drone &d, const Seg &seg, SweepMemo &memo) {
     constexpr int M = 64 / E;
     constexpr int H = (M - 1) / 2;
-    uint32_t bits = 0;
-    {
+    constexpr bool KEEP = E == 1;
+    uint32_t need = memo.need;
+    if (!KEEP || __ballot(valid && memo.moved(d)) != 0ull) {
+        uint32_t bits = 0;
         const KConst c = margin_consts(c0);
 #pragma unroll
         for (int k = 1; k <= H + 1; ++k) {
             const float4 q = own[E * k];
-            bits = push_sign(bits, dw_margin<DZMIN>(c, q.x - d.px, q.y - d.py, fabsf(q.z - d.pz)));
-            seg.template at<H>(k - 1);
+            bits = push_sign(bits, dw_margin<DZMIN, KEEP>(c, q.x - d.px, q.y - d.py, fabsf(q.z - d.pz)));
+        }
+        need = wave_or(valid ? bits : 0u) << (31 - H);  // shift k in bit 32 - k
+        if (KEEP) {
+            memo.need = need;
+            memo.stand(d);
         }
     }
-    // shift k in bit 32 - k
-    uint32_t need = wave_or(bits) << (31 - H);
+    need = (uint32_t)__builtin_amdgcn_readfirstlane((int)need);
     const bool half = (need >> (31 - H)) & 1u;
     need &= ~(1u << (31 - H));
-    dense = __builtin_popcount(need) > H / 2 ? SPARSE_RETRY - 1 : 0;
+    if (__builtin_popcount(need) > H / 2) {
+        memo.dense = SPARSE_RETRY - 1;
+        if (KEEP) memo.forget();
+    }
     const KConst c = pair_consts(c0);
     float acc = 0.f;
+    seg.all();
     while (need) {
         const int k = __builtin_clz(need) + 1;
         need &= ~(0x80000000u >> (k - 1));
@@ -403,32 +454,32 @@ __device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const flo
 }
 
 template <bool DZMIN, int E, bool TESTS, class Seg>
-__device__ __forceinline__ float dw_rot_size(const KConst &c, const float4 *own, int lane, const Drone &d,
-                                             const Seg &seg, int &dense) {
+__device__ __forceinline__ float dw_rot_size(const KConst &c, const float4 *own, int lane, bool valid, const Drone &d,
+                                             const Seg &seg, SweepMemo &memo) {
     if (TESTS && 64 / E >= SPARSE_MIN_ENV) {
-        dense = __builtin_amdgcn_readfirstlane(dense);
-        if (dense == 0) return dw_pairs_rot_sparse<DZMIN, E>(c, own, lane, d, seg, dense);
-        --dense;
+        if (__builtin_amdgcn_readfirstlane(memo.dense) == 0)
+            return dw_pairs_rot_sparse<DZMIN, E>(c, own, lane, valid, d, seg, memo);
+        --memo.dense;
     }
     return dw_pairs_rot<DZMIN, E>(c, own, lane, d, seg);
 }
 
 // TESTS: sweep by tests first where that pays.
 template <bool DZMIN, bool TESTS = true, class Seg = NoSeg>
-__device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int lane, int m, const Drone &d,
-                                        int &dense, const Seg &seg = Seg()) {
+__device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int lane, int m, bool valid, const Drone &d,
+                                        SweepMemo &memo, const Seg &seg = Seg()) {
     switch (m) {
         case 64: {
             // 31 shifts unrolled leave no registers for interleaved stores
-            const float r = dw_rot_size<DZMIN, 1, TESTS>(c, own, lane, d, NoSeg(), dense);
+            const float r = dw_rot_size<DZMIN, 1, TESTS>(c, own, lane, valid, d, NoSeg(), memo);
             seg.all();
             return r;
         }
-        case 32: return dw_rot_size<DZMIN, 2, TESTS>(c, own, lane, d, seg, dense);
-        case 16: return dw_rot_size<DZMIN, 4, TESTS>(c, own, lane, d, seg, dense);
-        case 8: return dw_rot_size<DZMIN, 8, TESTS>(c, own, lane, d, seg, dense);
-        case 4: return dw_rot_size<DZMIN, 16, TESTS>(c, own, lane, d, seg, dense);
-        default: return dw_rot_size<DZMIN, 32, TESTS>(c, own, lane, d, seg, dense);
+        case 32: return dw_rot_size<DZMIN, 2, TESTS>(c, own, lane, valid, d, seg, memo);
+        case 16: return dw_rot_size<DZMIN, 4, TESTS>(c, own, lane, valid, d, seg, memo);
+        case 8: return dw_rot_size<DZMIN, 8, TESTS>(c, own, lane, valid, d, seg, memo);
+        case 4: return dw_rot_size<DZMIN, 16, TESTS>(c, own, lane, valid, d, seg, memo);
+        default: return dw_rot_size<DZMIN, 32, TESTS>(c, own, lane, valid, d, seg, memo);
     }
 }
 
@@ -447,8 +498,10 @@ __device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int 
 // term costs a compare, a select, an add and a rotation more.
 // The order of a drone's sum depends only on its place in its environment.
 // 512 environments x 256 drones, 50 steps: 895 us with the all-pairs sweep,
-// 617 us with this one; bound by the vector ALU (busy 89 % of the time at the
-// two waves per SIMD that this layout gives, 4.4 cycles an instruction).
+// 617 us with every pair of this one evaluated, 175 us with tests that are
+// kept; with every pair evaluated it is bound by the vector ALU (busy 89 % of
+// the time at the two waves per SIMD that this layout gives, 4.4 cycles an
+// instruction).
 // dw_block sweeps and writes the sums for other waves; after a barrier
 // dw_block_rest adds those that other waves left for this one.
 //
@@ -518,30 +571,32 @@ __device__ __forceinline__ void dw_batches(const KConst &c, const float4 *q, int
     dw_batch<DZMIN, LAST_OWN>(c, B, d, acc, theirs);
 }
 
-// 32 shifts of a block from q on by tests first: the same terms onto the same
-// sums as dw_batches.  `theirs` belongs to the partner of shift `at` (both
-// counted from q) on entry and on return.  Returns the shifts evaluated.
-template <bool DZMIN, bool LAST_OWN>
-__device__ __forceinline__ int dw_block_sparse(const KConst &c0, const float4 *q, int lane, const Drone &d, float &acc,
-                                               float &theirs, int &at) {
+// The tests of 32 shifts of a block from q on: those that some lane needs,
+// shift k in bit 31 - k.
+template <bool DZMIN>
+__device__ __forceinline__ uint32_t dw_block_tests(const KConst &c0, const float4 *q, bool valid, const Drone &d) {
     uint32_t bits = 0;
-    {
-        const KConst c = margin_consts(c0);
+    const KConst c = margin_consts(c0);
 #pragma unroll 1
-        for (int k = 0; k < 32; k += 8) {
-            float x[8];
+    for (int k = 0; k < 32; k += 8) {
+        float x[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float4 p = q[k + u];
-                x[u] = dw_margin<DZMIN>(c, p.x - d.px, p.y - d.py, fabsf(p.z - d.pz));
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) bits = push_sign(bits, x[u]);
+        for (int u = 0; u < 8; ++u) {
+            const float4 p = q[k + u];
+            x[u] = dw_margin<DZMIN, true>(c, p.x - d.px, p.y - d.py, fabsf(p.z - d.pz));
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) bits = push_sign(bits, x[u]);
     }
-    uint32_t need = wave_or(bits);  // shift k in bit 31 - k
-    const int n = __builtin_popcount(need);
-    const KConst c = pair_consts(c0);
+    return wave_or(valid ? bits : 0u);
+}
+
+// The needed ones of 32 shifts from q on: the same terms onto the same sums as
+// dw_batches.  `theirs` belongs to the partner of shift `at` (both counted from
+// q) on entry and on return.
+template <bool DZMIN, bool LAST_OWN>
+__device__ __forceinline__ void dw_block_sparse(const KConst &c, uint32_t need, const float4 *q, int lane,
+                                                const Drone &d, float &acc, float &theirs, int &at) {
     while (need) {
         const int k = __builtin_clz(need);
         need &= ~(0x80000000u >> k);
@@ -556,51 +611,92 @@ __device__ __forceinline__ int dw_block_sparse(const KConst &c0, const float4 *q
         theirs = moved + ((near & (dz < 0.f)) ? t : 0.f);
         at = k;
     }
-    return n;
+}
+
+// The waves of an environment form their tests at the same step: each
+// publishes (in its positions' fourth component, before the step's barrier)
+// whether it asks for that, because one of its drones has moved or because its
+// steps without tests are over (memo.dense has come down to 1).
+__device__ __forceinline__ float dw_block_asks(const SweepMemo &memo, bool valid, const Drone &d) {
+    return memo.dense == 1 || __ballot(valid && memo.moved(d)) != 0ull ? 1.f : 0.f;
 }
 
 template <bool DZMIN>
 __device__ __forceinline__ float dw_block(const KConst &c0, const float4 *pos, float *sums, int slots, int slot,
-                                          int lo_lane, int m_lane, const Drone &d, int &dense) {
+                                          int lo_lane, int m_lane, bool valid, const Drone &d, SweepMemo &memo) {
     const int lane = slot & 63;
     const int lo = __builtin_amdgcn_readfirstlane(lo_lane);
     const int W = (__builtin_amdgcn_readfirstlane(m_lane) + 63) >> 6;
     const int a = (__builtin_amdgcn_readfirstlane(slot) - lo) >> 6;
     float acc = 0.f, theirs = 0.f;
     if (W == 0) return 0.f;
-    dense = __builtin_amdgcn_readfirstlane(dense);
-    const bool sparse = dense == 0;
+    // word 0: the wave's own 32 shifts; then two words per block of 64, one
+    // for the shared half block
     const float4 *own = pos + 2 * (lo + 64 * a) + lane + 1;
-    int evaluated = 0, at = 30;
+    auto block = [&](int dd, int &b, int &k0, bool &half) {
+        half = 2 * dd == W;
+        b = a + dd < W ? a + dd : a + dd - W;
+        k0 = half && b < a ? 1 : 0;
+        return pos + 2 * (lo + 64 * b) + lane + k0;
+    };
+    const bool asked = __ballot(lane < W && pos[2 * (lo + 64 * (lane < W ? lane : 0))].w > 0.f) != 0ull;
+    int dense = __builtin_amdgcn_readfirstlane(memo.dense);
+    if (asked) {
+        memo.stand(d);
+        if (dense <= 1) {
+            uint32_t words = 0, w = dw_block_tests<DZMIN>(c0, own, valid, d);
+            int n = 1, count = __builtin_popcount(w);
+            words = lane == 0 ? w : 0u;
+#pragma unroll 1
+            for (int dd = 1; dd <= W >> 1; ++dd) {
+                int b, k0;
+                bool half;
+                const float4 *q = block(dd, b, k0, half);
+#pragma unroll 1
+                for (int h = 0; h < (half ? 1 : 2); ++h) {
+                    w = dw_block_tests<DZMIN>(c0, q + 32 * h, valid, d);
+                    count += __builtin_popcount(w);
+                    words = lane == n ? w : words;
+                    ++n;
+                }
+            }
+            memo.need = words;
+            // 32 W shifts were tested
+            dense = count > 16 * W ? SPARSE_RETRY + 1 : 0;
+        }
+    }
+    memo.dense = max(dense - 1, 0);
+    const bool sparse = dense == 0;
+    auto word = [&](int k) { return (uint32_t)__builtin_amdgcn_readlane((int)memo.need, k); };
+    const KConst c = pair_consts(c0);
+    int at = 30;
     if (sparse)
-        evaluated += dw_block_sparse<DZMIN, true>(c0, own, lane, d, acc, theirs, at);
+        dw_block_sparse<DZMIN, true>(c, word(0), own, lane, d, acc, theirs, at);
     else
-        dw_batches<DZMIN, true>(pair_consts(c0), own, 32 / (2 * PAIR_BATCH), d, acc, theirs);
+        dw_batches<DZMIN, true>(c, own, 32 / (2 * PAIR_BATCH), d, acc, theirs);
     // shift at + 1's partner terms: lane - (at + 1)'s
     acc += __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (lane - 1 - at), __float_as_int(theirs)));
+    int n = 1;
 #pragma unroll 1
     for (int dd = 1; dd <= W >> 1; ++dd) {
-        const bool half = 2 * dd == W;
-        const int b = a + dd < W ? a + dd : a + dd - W;
-        const int k0 = half && b < a ? 1 : 0, n = half ? 32 : 64;
-        const float4 *q = pos + 2 * (lo + 64 * b) + lane + k0;
+        int b, k0;
+        bool half;
+        const float4 *q = block(dd, b, k0, half);
         theirs = 0.f;
-        at = n - 1;
+        at = half ? 31 : 63;
         if (sparse) {
             at = 0;
-            evaluated += dw_block_sparse<DZMIN, false>(c0, q, lane, d, acc, theirs, at);
+            dw_block_sparse<DZMIN, false>(c, word(n++), q, lane, d, acc, theirs, at);
             if (!half) {
                 at -= 32;
-                evaluated += dw_block_sparse<DZMIN, false>(c0, q + 32, lane, d, acc, theirs, at);
+                dw_block_sparse<DZMIN, false>(c, word(n++), q + 32, lane, d, acc, theirs, at);
                 at += 32;
             }
         } else {
-            dw_batches<DZMIN, false>(pair_consts(c0), q, n / (2 * PAIR_BATCH), d, acc, theirs);
+            dw_batches<DZMIN, false>(c, q, (half ? 32 : 64) / (2 * PAIR_BATCH), d, acc, theirs);
         }
         sums[(dd - 1) * slots + lo + 64 * b + ((lane + k0 + at) & 63)] = theirs;
     }
-    // 32 + (W - 1) 32 shifts were tested
-    dense = sparse ? (evaluated > 16 * W ? SPARSE_RETRY - 1 : 0) : dense - 1;
     return acc;
 }
 
@@ -620,11 +716,13 @@ __device__ __forceinline__ float dw_block_rest(const float *sums, int slots, int
 // to SYM 2).
 // SCAN: the one-lane sweep by tests first, in the kernels with wind or
 // randomisation, whose other work covers its latencies (4096 x 32 randomised
-// drones, 50 steps: 367 without, 346 us with it; the plain step 299 and 319).
-template <int LPD, int UNROLL, int SYM, bool TESTS = true, bool SCAN = false>
+// drones, 50 steps: 367 without, 333 us with it, 312 us with kept outcomes; the
+// plain step 299 and 319).  1: tests at every step (wind: 190 us, 2048 ragged
+// environments, 193 with kept outcomes), 2: outcomes kept (randomisation).
+template <int LPD, int UNROLL, int SYM, bool TESTS = true, int SCAN = 0>
 __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, float *tmat, int ts, int slots, int slot,
-                                        int sub, int lo, int mmax, int menv, bool uniform, const Drone &d,
-                                        int &dense) {
+                                        int sub, int lo, int mmax, int menv, bool uniform, bool valid,
+                                        const Drone &d, SweepMemo &memo) {
     float acc = 0.f;
     if constexpr (SYM == SWEEP_LANES) {
         return c.dz_min > 0.f ? dw_lanes<true, LPD>(c, buf, slots, lo, sub, mmax, menv, d)
@@ -635,8 +733,8 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
         // positions twice, 128 entries per wave
         const int lane = slot & 63;
         const float4 *own = buf + 2 * (slot - lane) + lane;
-        acc = c.dz_min > 0.f ? dw_rot<true, TESTS>(c, own, lane, mmax, d, dense)
-                             : dw_rot<false, TESTS>(c, own, lane, mmax, d, dense);
+        acc = c.dz_min > 0.f ? dw_rot<true, TESTS>(c, own, lane, mmax, valid, d, memo)
+                             : dw_rot<false, TESTS>(c, own, lane, mmax, valid, d, memo);
     } else if (SYM == 2) {
         // `uniform` and dz_min are the same for the whole workgroup: the
         // permutes inside run with every lane of the wave
@@ -661,14 +759,14 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
             acc += t.z;
             acc += t.w;
         }
-    } else if (SCAN && LPD == 1 && mmax >= SPARSE_MIN_ENV && (dense = __builtin_amdgcn_readfirstlane(dense)) == 0) {
-        acc = c.dz_min > 0.f ? dw_sweep_sparse<true>(c, buf, slots, lo, mmax, menv, d, dense)
-                             : dw_sweep_sparse<false>(c, buf, slots, lo, mmax, menv, d, dense);
+    } else if (SCAN && LPD == 1 && mmax >= SPARSE_MIN_ENV && __builtin_amdgcn_readfirstlane(memo.dense) == 0) {
+        acc = c.dz_min > 0.f ? dw_sweep_sparse<true, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo)
+                             : dw_sweep_sparse<false, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo);
     } else if (c.dz_min > 0.f) {
-        dense -= SCAN && dense > 0 ? 1 : 0;
+        memo.dense -= SCAN && memo.dense > 0 ? 1 : 0;
         acc = dw_sweep<true, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     } else {
-        dense -= SCAN && dense > 0 ? 1 : 0;
+        memo.dense -= SCAN && memo.dense > 0 ? 1 : 0;
         acc = dw_sweep<false, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     }
     // the partial sums of a drone's lanes, combined across the lanes of a
