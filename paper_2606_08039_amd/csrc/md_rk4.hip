@@ -84,6 +84,13 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
     int phase = (ACT >= 1) ? (int)(a.step0 % (long long)c.decim) : 0;
     int oslot = 0;
     SweepMemo memo;
+    // One body for the four stages where a sweep fills it: unrolled, the
+    // rotation's five sizes took 84 KB of code and the block sweep spilled (50
+    // steps, unrolled -> one body: 4096 x 32 drones 467 -> 420 us).  The sweeps
+    // through LDS or over single drones are faster unrolled (4096 x 1, 60
+    // steps: 58 us, one body 75).  The permute sweep goes with the rotation: the
+    // two are to round alike, so their multiply-adds must form alike.
+    constexpr bool ROLLED = SYM == 2 || SYM == 3 || SYM == SWEEP_BLOCK;
     const float half_dt = 0.5f * c.dt, sixth_dt = c.dt * (1.f / 6.f);
     for (int step = 0; step < a.n_steps; ++step) {
         // ---- rotor speeds, held over the step
@@ -105,7 +112,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
         // ---- four stages
         const Drone x0 = d;
         Drone ks{};  // k1 + 2 k2 + 2 k3 + k4
-#pragma unroll
+#pragma unroll(ROLLED ? 1 : 4)
         for (int st = 0; st < 4; ++st) {
             float4 *buf = lds_pos + (st & 1) * (2 * slots);
             if (MASK & 4u) {
@@ -148,11 +155,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
                     __syncthreads();
                     Fz -= c.K1 * dw_block_rest(sums, slots, slot, menv, part);
                 } else {
-                    // the rotation sweep without tests: with them the
-                    // compiler forms the stage's multiply-adds in other
-                    // places than around the permute sweep, and the two are
-                    // to round alike (453 against 470 us, 4096 x 32 drones)
-                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, false>(
+                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, 32, 0, true>(
                                      c, buf, tmat, a.tstride, slots, slot, 0, lo, mmax, menv, uniform, valid, d, memo);
                 }
             }

@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
                 __syncthreads();
                 acc = dw_block_rest(sums, slots, slot, menv, acc);
             } else {
-                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, true, DIST>(
+                acc = dw_sum<LPD, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, SPARSE_MIN_ENV, DIST>(
                     c, buf, tmat, a.tstride, slots, slot, sub, lo, mmax, menv, uniform, valid, d, memo);
             }
             Fz -= cl.K1 * acc;

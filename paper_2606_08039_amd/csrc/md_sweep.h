@@ -51,6 +51,8 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // 258 us; 2048 x 64, 60 steps with observations 200 -> 167 us, without 178 ->
 // 140 us; 4096 x 32 randomised, 50 steps 333 -> 312 us.
 constexpr int SPARSE_RETRY = 8;
+// Pairs evaluated side by side where a sweep goes by batches.
+constexpr int PAIR_BATCH = 4;
 // Smallest environment that takes tests: at 32 drones a third of the 16 shifts
 // is needed by some lane and the tests pay a little; at 16 they do not (223
 // without, 226 us with them, 8192 environments, 100 steps with observations).
@@ -396,17 +398,97 @@ __device__ __forceinline__ float dw_pairs_rot(const KConst &c0, const float4 *ow
     return acc;
 }
 
+// The same sum PAIR_BATCH shifts at a time (the last one of all, by M / 2, has
+// no received term: that pair is evaluated by both of its drones): the next
+// positions are on their way from LDS while these are evaluated, and terms from
+// other lanes are added a batch later.  In the Runge-Kutta kernel the compiler
+// otherwise evaluates one shift after the other, and each waits out both
+// latencies (50 steps, serial -> batched: 8192 x 16 drones 314 -> 261 us, 4096
+// x 32 547 -> 430 us); around the Euler step it overlaps them by itself, and
+// batches would spill.
+template <bool DZMIN, int E>
+__device__ __forceinline__ float dw_pairs_rot_batched(const KConst &c0, const float4 *own, int lane,
+                                                      const Drone &d) {
+    constexpr int M = 64 / E;
+    constexpr int H = (M - 1) / 2;
+    const KConst c = pair_consts(c0);
+    // the permute addresses pa + 256 - 4 E k fold into the instructions'
+    // offset field when pa is formed inside the step: hoisted out of the
+    // step loop instead, they would hold one register per shift
+    int pa = 4 * lane;
+    asm volatile("" : "+v"(pa));
+    constexpr int B = M / 2 < PAIR_BATCH ? M / 2 : PAIR_BATCH;
+    float x[B], y[B], z[B], mine[B], recv[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+        const float4 q = own[E * (1 + u)];
+        x[u] = q.x;
+        y[u] = q.y;
+        z[u] = q.z;
+    }
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 1; k <= H + 1; k += B) {
+        float dz[B], d2[B], t[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            dz[u] = z[u] - d.pz;
+            d2[u] = dw_d2(x[u] - d.px, y[u] - d.py);
+            if (k + B <= H + 1) {
+                const float4 q = own[E * (k + B + u)];
+                x[u] = q.x;
+                y[u] = q.y;
+                z[u] = q.z;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) t[u] = dw_raw<DZMIN>(c, d2[u], fabsf(dz[u]));
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            asm volatile("" : "+v"(t[u]));  // formed before the first select
+        }
+        if (k > 1) {
+#pragma unroll
+            for (int u = 0; u < B; ++u) {
+                acc += mine[u];
+                acc += recv[u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const bool near = dw_near(d2[u]);
+            mine[u] = (near && dz[u] > 0.f) ? t[u] : 0.f;
+            // formed here, not where the serial sum reaches it: otherwise its
+            // lane mask stays live across shifts and the masks spill
+            asm volatile("" : "+v"(mine[u]));
+            if (k + u > H) break;
+            const float theirs = (near && dz[u] < 0.f) ? t[u] : 0.f;
+            recv[u] =
+                __int_as_float(__builtin_amdgcn_ds_bpermute(pa + (256 - 4 * E * (k + u)), __float_as_int(theirs)));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+        acc += mine[u];
+        if (u < B - 1) acc += recv[u];
+    }
+    return acc;
+}
+
 // The same sum, bit for bit, from the shifts that some lane of the wave needs,
-// ascending.  With 64 drones the outcomes are kept until a drone has moved;
-// with 32 the tests are run at every step: sixteen cost no more than keeping
-// their outcomes (8192 x 32 drones, 60 steps with observations: 276 us run,
-// 284-300 us kept; 2048 x 64 178 run, 139 us kept).
-template <bool DZMIN, int E, class Seg>
+// ascending.  KEEP: the outcomes are kept until a drone has moved.  The Euler
+// step of 32 drones runs its sixteen tests every time, which costs no more
+// than keeping their outcomes (8192 x 32 drones, 60 steps with observations:
+// 276 us run, 284-300 us kept; 2048 x 64 178 run, 139 us kept).  The stages of
+// a Runge-Kutta step lie close together and keep them (50 steps, every pair
+// evaluated -> kept: 8192 x 32 690 -> 593 us, 4096 x 32 421 -> 430 us, 2048 x
+// 64 641 -> 412 us).
+template <bool DZMIN, int E, bool KEEP, class Seg>
 __device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const float4 *own, int lane, bool valid,
                                                      const Drone &d, const Seg &seg, SweepMemo &memo) {
     constexpr int M = 64 / E;
     constexpr int H = (M - 1) / 2;
-    constexpr bool KEEP = E == 1;
     uint32_t need = memo.need;
     if (!KEEP || __ballot(valid && memo.moved(d)) != 0ull) {
         uint32_t bits = 0;
@@ -453,33 +535,34 @@ __device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const flo
     return acc;
 }
 
-template <bool DZMIN, int E, bool TESTS, class Seg>
+template <bool DZMIN, int E, int TESTS, bool BATCHED, class Seg>
 __device__ __forceinline__ float dw_rot_size(const KConst &c, const float4 *own, int lane, bool valid, const Drone &d,
                                              const Seg &seg, SweepMemo &memo) {
-    if (TESTS && 64 / E >= SPARSE_MIN_ENV) {
+    if (64 / E >= TESTS) {
         if (__builtin_amdgcn_readfirstlane(memo.dense) == 0)
-            return dw_pairs_rot_sparse<DZMIN, E>(c, own, lane, valid, d, seg, memo);
+            return dw_pairs_rot_sparse<DZMIN, E, E == 1 || BATCHED>(c, own, lane, valid, d, seg, memo);
         --memo.dense;
     }
+    if constexpr (BATCHED && E > 1) return dw_pairs_rot_batched<DZMIN, E>(c, own, lane, d);
     return dw_pairs_rot<DZMIN, E>(c, own, lane, d, seg);
 }
 
-// TESTS: sweep by tests first where that pays.
-template <bool DZMIN, bool TESTS = true, class Seg = NoSeg>
+// TESTS: the smallest environment that is swept by tests first.
+template <bool DZMIN, int TESTS = SPARSE_MIN_ENV, bool BATCHED = false, class Seg = NoSeg>
 __device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int lane, int m, bool valid, const Drone &d,
                                         SweepMemo &memo, const Seg &seg = Seg()) {
     switch (m) {
         case 64: {
             // 31 shifts unrolled leave no registers for interleaved stores
-            const float r = dw_rot_size<DZMIN, 1, TESTS>(c, own, lane, valid, d, NoSeg(), memo);
+            const float r = dw_rot_size<DZMIN, 1, TESTS, BATCHED>(c, own, lane, valid, d, NoSeg(), memo);
             seg.all();
             return r;
         }
-        case 32: return dw_rot_size<DZMIN, 2, TESTS>(c, own, lane, valid, d, seg, memo);
-        case 16: return dw_rot_size<DZMIN, 4, TESTS>(c, own, lane, valid, d, seg, memo);
-        case 8: return dw_rot_size<DZMIN, 8, TESTS>(c, own, lane, valid, d, seg, memo);
-        case 4: return dw_rot_size<DZMIN, 16, TESTS>(c, own, lane, valid, d, seg, memo);
-        default: return dw_rot_size<DZMIN, 32, TESTS>(c, own, lane, valid, d, seg, memo);
+        case 32: return dw_rot_size<DZMIN, 2, TESTS, BATCHED>(c, own, lane, valid, d, seg, memo);
+        case 16: return dw_rot_size<DZMIN, 4, TESTS, BATCHED>(c, own, lane, valid, d, seg, memo);
+        case 8: return dw_rot_size<DZMIN, 8, TESTS, BATCHED>(c, own, lane, valid, d, seg, memo);
+        case 4: return dw_rot_size<DZMIN, 16, TESTS, BATCHED>(c, own, lane, valid, d, seg, memo);
+        default: return dw_rot_size<DZMIN, 32, TESTS, BATCHED>(c, own, lane, valid, d, seg, memo);
     }
 }
 
@@ -509,7 +592,6 @@ __device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int 
 // while the previous one is evaluated, and its reciprocals and exponentials
 // overlap one another (one pair after the other, each waits out the LDS and
 // the two transcendental latencies: two waves per SIMD do not cover them).
-constexpr int PAIR_BATCH = 4;
 
 struct PairBatch {
     float x[PAIR_BATCH], y[PAIR_BATCH], z[PAIR_BATCH];
@@ -719,7 +801,7 @@ __device__ __forceinline__ float dw_block_rest(const float *sums, int slots, int
 // drones, 50 steps: 367 without, 333 us with it, 312 us with kept outcomes; the
 // plain step 299 and 319).  1: tests at every step (wind: 190 us, 2048 ragged
 // environments, 193 with kept outcomes), 2: outcomes kept (randomisation).
-template <int LPD, int UNROLL, int SYM, bool TESTS = true, int SCAN = 0>
+template <int LPD, int UNROLL, int SYM, int TESTS = SPARSE_MIN_ENV, int SCAN = 0, bool BATCHED = false>
 __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, float *tmat, int ts, int slots, int slot,
                                         int sub, int lo, int mmax, int menv, bool uniform, bool valid,
                                         const Drone &d, SweepMemo &memo) {
@@ -733,8 +815,8 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
         // positions twice, 128 entries per wave
         const int lane = slot & 63;
         const float4 *own = buf + 2 * (slot - lane) + lane;
-        acc = c.dz_min > 0.f ? dw_rot<true, TESTS>(c, own, lane, mmax, valid, d, memo)
-                             : dw_rot<false, TESTS>(c, own, lane, mmax, valid, d, memo);
+        acc = c.dz_min > 0.f ? dw_rot<true, TESTS, BATCHED>(c, own, lane, mmax, valid, d, memo)
+                             : dw_rot<false, TESTS, BATCHED>(c, own, lane, mmax, valid, d, memo);
     } else if (SYM == 2) {
         // `uniform` and dz_min are the same for the whole workgroup: the
         // permutes inside run with every lane of the wave

@@ -15,13 +15,15 @@ STEPS = 48
 LAYOUTS = {
     # name: (environments, lattice, thinned, configuration)
     "rotation64": (13, (8, 4, 2), False, dict(waves_per_group=1, pair_symmetric=3)),
+    "rotation32": (25, (4, 4, 2), False, dict(waves_per_group=1, pair_symmetric=3)),
+    "rotation16": (25, (4, 2, 2), False, dict(waves_per_group=1, pair_symmetric=3)),
     "block128": (5, (8, 8, 2), False, None),
     "block_ragged": (6, (10, 10, 2), True, None),
     "randomized32": (21, (4, 4, 2), False, dict(waves_per_group=1, pair_symmetric=0)),
     "randomized_ragged": (21, (4, 4, 2), True, dict(waves_per_group=1, pair_symmetric=0)),
 }
-# (the Runge-Kutta kernel keeps outcomes in the block sweep only)
-CASES = [(name, "euler") for name in sorted(LAYOUTS)] + [("block128", "rk4"), ("block_ragged", "rk4")]
+CASES = [(name, kind) for name in sorted(LAYOUTS) for kind in ("euler", "rk4")
+         if not (kind == "rk4" and name.startswith("randomized"))]
 
 
 @pytest.mark.parametrize("speed", [0.0, 0.6, 15.0])
@@ -53,5 +55,24 @@ def test_one_launch_equals_single_steps(layout, kind, scale, speed):
         g.close()
     # (a randomised drone that starts at 15 m/s leaves the model's range, in
     # the oracle too, and its position becomes a NaN: compared like any value)
+    for k in ("p", "q", "v", "w", "rpm", "pid_int"):
+        np.testing.assert_array_equal(got[1][k], got[0][k])
+
+
+@pytest.mark.parametrize("shape", [(2, 1, 1), (1, 2, 2), (2, 2, 2)])
+def test_small_runge_kutta_rotation_equals_permute(shape):
+    """The rotation by batches where an environment has fewer shifts than a
+    batch, or one batch exactly."""
+    w = wl.lattice(n_envs=101, shape=shape, n_steps=STEPS, seed=24)
+    w["state"]["p"][:2] *= np.float32(0.2)
+    w["action"][:, :2] *= np.float32(0.2)
+    w["integrator"] = "rk4"
+    got = []
+    for sym in (2, 3):
+        print("%s sweep %d" % (shape, sym), flush=True)
+        g = pu.DeviceRun(w, cfg=dict(lanes_per_drone=1, unroll=1, waves_per_group=1, pair_symmetric=sym))
+        g.run(STEPS)
+        got.append(g.snapshot())
+        g.close()
     for k in ("p", "q", "v", "w", "rpm", "pid_int"):
         np.testing.assert_array_equal(got[1][k], got[0][k])
