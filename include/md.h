@@ -164,8 +164,10 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
  * Each drone's downwash terms are summed in an order fixed by the launch
  * configuration and the drone's place in its environment (ascending drone
  * order for lanes_per_drone 1 with pair_symmetric 0 or 1, in environments of
- * more than 112 drones block by block of 64; see md_launch_config), so results do not depend on how environments are packed
- * or on how a rollout is split into launches.  Errors: MD_E_LAYOUT if no
+ * more than 112 drones block by block of 64; see md_launch_config), so results
+ * do not depend on how environments are packed or on how a rollout is split
+ * into launches.  The configuration that binding a layout gives may run a small
+ * layout with 4 or 8 lanes per drone in that same ascending order.  Errors: MD_E_LAYOUT if no
  * layout is bound, MD_E_INVALID_ARG for null required pointers or
  * n_steps < 0. */
 md_status md_step(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
@@ -321,10 +323,11 @@ typedef struct md_launch_config {
     int lanes_per_drone; /* 1, 2 or 4 lanes share one drone's neighbour sweep */
     int unroll;          /* neighbour-loop unroll: 1, 2 or 4 (1 for pair_symmetric 2 and 3) */
     int waves_per_group; /* 1, 2, 4, 8 or 16 wave64s per workgroup (bin of 64*w/lpd slots); with
-                            pair_symmetric 3 every wave is a workgroup, whatever the bin */
+                            pair_symmetric 3 a launch that is short, stores no rows or does not
+                            fill the GPU runs every wave as a workgroup of its own */
     int pair_symmetric;  /* 0: all ordered pairs (one lane per drone and environments of more
-                            than 112 drones: each unordered pair once, block by block); 1: each unordered pair once, terms routed
-                            through an LDS matrix; 2: each unordered pair once, terms routed
+                            than 112 drones: each unordered pair once, block by block); 1: each
+                            unordered pair once, terms routed through an LDS matrix; 2: each unordered pair once, terms routed
                             between lanes by wave permutes (environments of at most 64
                             drones, packed so that none crosses a wavefront; unroll 1); 3: the
                             pairs of 2 as rotations of the whole wave, for layouts whose

@@ -22,7 +22,7 @@ namespace {
 using namespace phys;
 
 template <uint32_t MASK, int ACT, int UNROLL, int SYM>
-__global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_kernel(StepArgs a) {
+__global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
     extern __shared__ float4 lds_pos[];  // [2][2 * slots] positions; then T [slots][tstride] (SYM)
     const KConst &c = a.c;
     const int slots = blockDim.x;
@@ -34,7 +34,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
     const int menv = tab.y & 0xffff;
     // each wave of the rotation sweep is a workgroup of its own (md_step_kernel.h)
     const int mm_word = a.bins.bin_mmax[SYM == 3 ? 0 : blockIdx.x];
-    if (SYM == 3 && __ballot(valid) == 0ull) return;
+    if (SYM == 3 && blockDim.x == 64 && __ballot(valid) == 0ull) return;
     const int mmax = mm_word & 0xffff;
     const bool uniform = ((mm_word >> 16) & 1) != 0;
     const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
@@ -84,6 +84,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
     int phase = (ACT >= 1) ? (int)(a.step0 % (long long)c.decim) : 0;
     int oslot = 0;
     SweepMemo memo;
+    if (SYM == 3 && blockDim.x > 64 && mmax <= 32) memo.dense = 1 << 30;  // (see rot_threads)
     // One body for the four stages where a sweep fills it: unrolled, the
     // rotation's five sizes took 84 KB of code and the block sweep spilled (50
     // steps, unrolled -> one body: 4096 x 32 drones 467 -> 420 us).  The sweeps
@@ -155,7 +156,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : 1024, SYM == 3 ? 4 : 1) rk4_ke
                     __syncthreads();
                     Fz -= c.K1 * dw_block_rest(sums, slots, slot, menv, part);
                 } else {
-                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, 32, 0, true>(
+                    Fz -= c.K1 * dw_sum<1, SYM == SWEEP_BLOCK ? 4 : UNROLL, SYM == SWEEP_BLOCK ? 0 : SYM, SPARSE_MIN_ENV, 0, true>(
                                      c, buf, tmat, a.tstride, slots, slot, 0, lo, mmax, menv, uniform, valid, d, memo);
                 }
             }
@@ -261,10 +262,11 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.unroll != 1) return hipErrorInvalidValue;
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, SWEEP_BLOCK>), dim3(n_bins), dim3(threads), lds, st, a);
-            else if (cfg.sym == 3)
-                hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins * threads / 64), dim3(64),
-                                   lds * 64 / threads, st, a);
-            else
+            else if (cfg.sym == 3) {
+                const int wg = rot_threads(a, n_bins, threads, true);
+                hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins * threads / wg),
+                                   dim3(wg), lds * wg / threads, st, a);
+            } else
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 2>), dim3(n_bins), dim3(threads), lds, st, a);
             return hipGetLastError();
         default: return hipErrorInvalidValue;

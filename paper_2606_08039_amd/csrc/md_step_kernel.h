@@ -258,8 +258,7 @@ struct RowSeg {
 // registers per lane that sixteen waves per workgroup leave (they spilled to
 // scratch memory, which the long launches then streamed through HBM).
 template <uint32_t MASK, int ACT, int LPD, int UNROLL, int SYM, int DIST>
-__global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1024,
-                                  SYM == 3 ? (DIST == 2 ? 2 : 4) : 1) step_kernel(StepArgs a) {
+__global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel(StepArgs a) {
     extern __shared__ float4 lds_pos[];  // [2][2 * slots] positions; then T [slots][tstride] (SYM)
     const KConst &c = a.c;
     const int slots = blockDim.x / LPD;
@@ -270,14 +269,10 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
     const bool valid = di >= 0;
     const int lo = tab.y >> 16;
     const int menv = tab.y & 0xffff;
-    // the rotation sweep's waves are independent: each is a workgroup of its
-    // own, whatever the bins' size, and every bin reports the same M.  Larger
-    // groups idle CUs where there are fewer than a few groups per CU (16384 x
-    // 8 drones, 100 steps: 243 us against 310 and 528 us in groups of 8 and 16
-    // waves) and wait for one another's tested pairs (8192 x 32, 1000 steps
-    // with observations: 5.00 ms against 5.28 and 5.15 ms)
+    // (the rotation sweep's workgroups may be smaller than its bins, which all
+    // report the same M)
     const int mm_word = a.bins.bin_mmax[SYM == 3 ? 0 : blockIdx.x];
-    if (SYM == 3 && __ballot(valid) == 0ull) return;
+    if (SYM == 3 && blockDim.x == 64 && __ballot(valid) == 0ull) return;
     const int mmax = mm_word & 0xffff;
     const bool uniform = ((mm_word >> 16) & 1) != 0;
     const bool block = SYM == SWEEP_BLOCK && (mm_word >> 17) != 0;  // whole-wave environments
@@ -415,6 +410,7 @@ __global__ void __launch_bounds__(SYM == 3 ? 64 : DIST == 2 ? MAX_THREADS_DR : 1
     bool motor_due = true;  // uniform
     float T = 0.f, tx = 0.f, ty = 0.f, tz = 0.f;
     SweepMemo memo;
+    if (seg_on && blockDim.x > 64 && mmax <= 32) memo.dense = 1 << 30;  // (see rot_threads)
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
         if (MASK & 4u) {
@@ -682,10 +678,11 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.unroll != 1) return hipErrorInvalidValue;
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, SWEEP_BLOCK, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
-            else if (cfg.sym == 3)
-                hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins * threads / 64), dim3(64),
-                                   lds * 64 / threads, st, a);
-            else
+            else if (cfg.sym == 3) {
+                const int wg = rot_threads(a, n_bins, threads, DIST == 0);
+                hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins * threads / wg),
+                                   dim3(wg), lds * wg / threads, st, a);
+            } else
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 2, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
             return hipGetLastError();
         }

@@ -81,7 +81,6 @@ static std::vector<LaunchCfg> candidates(const md_ctx *ctx) {
             for (int w : {1, 2, 4, 8, 16})
                 for (int u : {1, 2, 4}) {
                     LaunchCfg c{lpd, u, w, sym};
-                    if (sym == 3 && w > 1) continue;  // its waves run as workgroups of their own
                     if (cfg_valid(ctx, c)) out.push_back(c);
                 }
     return out;

@@ -76,3 +76,24 @@ def test_small_runge_kutta_rotation_equals_permute(shape):
         g.close()
     for k in ("p", "q", "v", "w", "rpm", "pid_int"):
         np.testing.assert_array_equal(got[1][k], got[0][k])
+
+
+@pytest.mark.parametrize("kind", ["euler", "rk4"])
+@pytest.mark.parametrize("n_envs,shape", [(8192, (4, 4, 2)), (16384, (4, 2, 2)), (4096, (8, 4, 2))])
+def test_long_launch_equals_short_ones(n_envs, shape, kind):
+    """A long launch with rows that fills the chip takes workgroups of several
+    waves, and up to 32 drones no tests; its parts take one wave each."""
+    w = wl.lattice(n_envs=n_envs, shape=shape, n_steps=750, seed=25)
+    if kind == "rk4":
+        w["integrator"] = "rk4"
+    got = []
+    for chunk in (750, 375):
+        print("%d x %s %s: %d steps a launch" % (n_envs, shape, kind, chunk), flush=True)
+        g = pu.DeviceRun(w, cfg=dict(lanes_per_drone=1, unroll=1, waves_per_group=16, pair_symmetric=3))
+        for _ in range(750 // chunk):
+            obs = g.run(chunk, obs_slots=3)
+        got.append((g.snapshot(), obs))
+        g.close()
+    np.testing.assert_array_equal(got[1][1], got[0][1])
+    for k in ("p", "q", "v", "w", "rpm", "pid_int"):
+        np.testing.assert_array_equal(got[1][0][k], got[0][0][k])
