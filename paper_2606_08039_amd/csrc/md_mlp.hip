@@ -246,7 +246,10 @@ __global__ void __launch_bounds__(256, 2) mlp_dgrad_kernel(DgradArgs a) {
     __shared__ __attribute__((aligned(16))) bf16 ds[2][16 * LDH];
     __shared__ float red[2][96];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    for (int i = tid; i < 16 * LDY; i += 256) dy[i] = (bf16)0.f;  // the outputs padded to k = 32
+    // the outputs padded to k = 32: the padding alone, since the outputs'
+    // elements are written by other threads before the first barrier
+    for (int i = tid; i < 16 * LDY; i += 256)
+        if (i % LDY >= MLP_OUT) dy[i] = (bf16)0.f;
     bf16x8 W4[2], W3[2][4], W2[2][4];
     auto frag = [&](int off, int tile, int kcs, int kc) {
         return *(const bf16x8 *)(a.W + off + ((tile * kcs + kc) * 64 + lane) * 8);
