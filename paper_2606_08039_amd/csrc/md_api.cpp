@@ -57,14 +57,15 @@ KConst make_kconst(const md_params &p, const md_derived &d, double dt, int decim
     c.c_xy = (float)p.c_xy;
     c.c_z = (float)p.c_z;
     c.K1 = (float)(p.C1 * p.r_p * p.r_p / 16.0);
-    c.C2 = (float)p.C2;
     c.C3 = (float)p.C3;
     c.dz_min = (float)std::max(0.0, p.dw_dz_min);
     c.C2s = (float)(std::sqrt(2.0 * std::log(2.0)) * p.C2);
     c.C3s = (float)(std::sqrt(2.0 * std::log(2.0)) * p.C3);
     c.C2c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C2);
     c.C3c = (float)(std::sqrt(320.0 * std::log(2.0)) * p.C3);
-    c.reach = (float)((std::sqrt(320.0 * std::log(2.0)) * std::fabs(p.C2) + 1.0) * 2.0 * MEMO_MOVE * 1.001);
+    const double D = std::ldexp(std::fabs((double)c.C3c), -22);
+    c.reach = (float)((std::sqrt(320.0 * std::log(2.0)) * std::fabs(p.C2) + 1.0) * 2.0 * MEMO_MOVE * 1.001 + D);
+    c.margin0 = (float)(1.6e-28 + 32.0 * D * D);
     for (int k = 0; k < 3; ++k) {
         c.pkp[k] = (float)p.pos_kp[k];
         c.pki[k] = (float)p.pos_ki[k];

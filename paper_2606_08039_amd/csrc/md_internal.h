@@ -17,9 +17,9 @@ struct KConst {
     float Jx, Jy, Jz, Jx_inv, Jy_inv, Jz_inv;
     float max_rpm, h_clip, K_gnd;         // K_gnd = C_gnd r_p^2 / 16   (Eq. 4)
     float drag_s, c_xy, c_z;              // drag_s = 2 pi / 60         (Eq. 5)
-    float K1, C2, C3, dz_min;             // K1 = C1 r_p^2 / 16         (Eq. 6)
+    float K1, margin0, C3, dz_min;        // K1 = C1 r_p^2 / 16         (Eq. 6); see dw_margin
     float C2s, C3s;                       // sqrt(2 ln 2) C2, sqrt(2 ln 2) C3
-    float C2c, C3c, reach;                // sqrt(160) times these; (|C2c| + 1) 2 MEMO_MOVE (dw_margin)
+    float C2c, C3c, reach;                // sqrt(160) times these; (|C2c| + 1) 2 MEMO_MOVE + 2^-22 |C3c|
     float pkp[3], pki[3], pkd[3], p_clamp;
     float akp[3], aki[3], akd[3], a_clamp;
     float dsl_pkp[3], dsl_pki[3], dsl_pkd[3], dsl_p_clamp;

@@ -347,19 +347,26 @@ __device__ __forceinline__ float dw_raw(const KConst &c, float d2, float adz) {
 __device__ __forceinline__ bool dw_near(float d2) { return d2 < 100.f; }
 
 // Negative when the pair's term may differ from 0 (the sign bit is the test):
-// d2 - 160 beta'^2 - 1.6e-28, which dw_raw's exponent -d2 / (beta'^2 + 1e-30)
+// d2 - 160 beta'^2 - margin0, which dw_raw's exponent -d2 / (beta'^2 + 1e-30)
 // then keeps above -160.  Where it is not negative, the exponent lies below
-// -159 (a few roundings), 2^x is 0 (the smallest denormal is 2^-149) and so is
-// the term.  A NaN position passes or not; its terms are gated to 0 anyway.
+// -150, 2^x is 0 (the smallest denormal is 2^-149) and so is the term.  Between
+// -150 and -160 lie the roundings: C2c, C3c are rounded apart from dw_raw's
+// C2s, C3s, so where C2 dz + C3 cancels (0.6875 m with the CF2X constants) the
+// two betas differ by up to D = 2^-22 |C3c|, which may be all of either.
+// 150/160 b^2 < (b - D)^2 + margin0 for every b = sqrt(160) beta' holds from
+// margin0 = 1.6e-28 + 16 D^2 on; make_kconst takes twice that (a lateral
+// distance of 2 um, for nothing but the roundings).  A NaN position passes or
+// not; its terms are gated to 0 anyway.
 // KEPT: the radius is widened by `reach`, so that the outcome holds for the
 // pair as long as neither drone has moved MEMO_MOVE: the offset changes by at
-// most 2 MEMO_MOVE, the radius sqrt(160) beta' by C2c times that.
+// most 2 MEMO_MOVE, the radius sqrt(160) beta' by C2c times that.  (`reach`
+// also holds D, and margin0 is not needed.)
 template <bool DZMIN, bool KEPT>
 __device__ __forceinline__ float dw_margin(const KConst &c, float dx, float dy, float adz) {
     const float dze = DZMIN ? fmaxf(adz, c.dz_min) : adz;
     float bc = fmaf(c.C2c, dze, c.C3c);
     if (KEPT) bc = fabsf(bc) + c.reach;
-    return fmaf(-bc, bc, fmaf(dx, dx, fmaf(dy, dy, -1.6e-28f)));
+    return fmaf(-bc, bc, fmaf(dx, dx, fmaf(dy, dy, KEPT ? -1.6e-28f : -c.margin0)));
 }
 
 template <bool DZMIN>
