@@ -166,7 +166,9 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
  * order for lanes_per_drone 1 with pair_symmetric 0 or 1, in environments of
  * more than 112 drones block by block of 64; see md_launch_config), so results
  * do not depend on how environments are packed or on how a rollout is split
- * into launches.  The configuration that binding a layout gives may run a small
+ * into launches (exception: with dw_dz_min 0, drones whose heights differ by
+ * less than 5.4e-20 m but not by 0, where the model's 1/dz^2 leaves the range
+ * of float32 and a partner outside the wake adds a NaN or nothing).  The configuration that binding a layout gives may run a small
  * layout with 4 or 8 lanes per drone in that same ascending order.  Errors: MD_E_LAYOUT if no
  * layout is bound, MD_E_INVALID_ARG for null required pointers or
  * n_steps < 0. */

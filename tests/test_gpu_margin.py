@@ -55,3 +55,24 @@ def test_no_needed_pair_is_left_out(kind, step):
         got = _run(w, 3 if kind == "euler" else 0, 1, steps)
         for k in ("p", "q", "v", "w", "rpm", "pid_int"):
             np.testing.assert_array_equal(got[k], ref[k], err_msg=k)
+
+
+def test_heights_next_to_zero_with_a_bounded_gap():
+    """Heights 0 and 1e-21: with dw_dz_min the term stays finite and a partner
+    outside the wake adds 0, evaluated or not."""
+    w = _stacked(0, 50)
+    p = w["state"]["p"].reshape(3, 6, 32)
+    p[0, :, 16:] += np.float32(0.1)
+    p[2, :, :16] = 0.0
+    p[2, :, 16:] = np.float32(1e-21)
+    par = pu.params()
+    par.dw_dz_min = 0.01
+    got = []
+    for sym in (2, 3):
+        g = pu.DeviceRun(w, p=par, cfg=dict(lanes_per_drone=1, unroll=1, waves_per_group=1, pair_symmetric=sym))
+        g.run(2)
+        got.append(g.snapshot())
+        g.close()
+    for k in ("p", "q", "v", "w", "rpm", "pid_int"):
+        assert np.isfinite(got[0][k]).all()
+        np.testing.assert_array_equal(got[1][k], got[0][k], err_msg=k)
