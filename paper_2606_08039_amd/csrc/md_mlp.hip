@@ -535,6 +535,19 @@ struct md_mlp {
 
 namespace {
 
+// The network's device current for a scope, the caller's afterwards.
+struct OnDevice {
+    int caller = -1;
+    explicit OnDevice(int device) {
+        (void)hipGetDevice(&caller);
+        if (caller != device) (void)hipSetDevice(device);
+        else caller = -1;
+    }
+    ~OnDevice() {
+        if (caller >= 0) (void)hipSetDevice(caller);
+    }
+};
+
 md_status mlp_fail(md_mlp *m, md_status st, const std::string &msg) {
     m->err = msg;
     return st;
@@ -608,6 +621,8 @@ const char *md_mlp_last_error(const md_mlp *m) { return m ? m->err.c_str() : "nu
 
 md_status md_mlp_set_params(md_mlp *m, const float *h_params) {
     if (!m || !h_params) return MD_E_INVALID_ARG;
+    // copies find their device by the address, the packing kernel does not
+    const OnDevice on(m->device);
     hipError_t e = hipMemcpy(m->params, h_params, sizeof(float) * md::MLP_NPARAMS, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(m->m1, 0, sizeof(float) * md::MLP_NPARAMS);
     if (e == hipSuccess) e = hipMemset(m->m2, 0, sizeof(float) * md::MLP_NPARAMS);
