@@ -307,8 +307,8 @@ void free_bins(md_ctx *ctx) {
 // How a configuration is launched: which bins, and the library's own sweeps in
 // place of the one-lane all-pairs one where they are the better way to the
 // same sums.  `choose`: the configuration is the layout's default and not the
-// caller's choice.
-LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
+// caller's choice; `plain`: the Euler step without wind or randomisation.
+static LaunchPlan plan_of(const md_ctx *ctx, const LaunchCfg &cfg, bool choose, bool plain) {
     LaunchPlan p{cfg, 64 * cfg.waves, BIN_PACKED};
     if (!(ctx->mask & MD_AERO_DW)) return p;
     p.slots = 64 * cfg.waves / cfg.lpd;
@@ -322,7 +322,7 @@ LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
         // bin stays idle behind it
         const int w = (ctx->max_m + 63) / 64;
         p.slots = 64 * w * std::max(1, cfg.waves / w);
-    } else if (choose && ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models && ctx->max_m > 1) {
+    } else if (choose && plain && ctx->max_m > 1) {
         // Several lanes per drone where one each would leave SIMDs without a
         // wave (a wave per SIMD is 65536 lanes).  Measured, us per 100 steps
         // with 1 / 4 / 8 lanes: M = 32, 8192 drones 221 / 129 / 100, 16384
@@ -340,6 +340,10 @@ LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
         }
     }
     return p;
+}
+
+LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
+    return plan_of(ctx, cfg, choose, ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models);
 }
 
 LaunchCfg default_cfg(const md_ctx *ctx) {
@@ -362,6 +366,20 @@ md_status prepare_launch(md_ctx *ctx) {
     }
     const LaunchPlan p = plan_for(ctx, ctx->cfg, !ctx->tuned);
     return build_bins(ctx, p.slots, p.mode, &bs);
+}
+
+// The tables of a newly bound layout's default configuration: for the plain
+// step, for the kernels with wind, randomisation or Runge-Kutta stages, and the
+// packed ones that the learned residual and md_datagen read.  A caller may
+// switch between all of these, and capture any call, without another upload.
+static md_status prepare_default(md_ctx *ctx) {
+    BinSet *bs = nullptr;
+    md_status rc = build_bins(ctx, 64 * ctx->cfg.waves, BIN_PACKED, &bs);
+    for (bool plain : {false, true}) {
+        const LaunchPlan p = plan_of(ctx, ctx->cfg, true, plain);
+        if (rc == MD_OK) rc = build_bins(ctx, p.slots, p.mode, &bs);
+    }
+    return rc;
 }
 
 // The step kernel of the context's integrator and disturbances.
@@ -586,7 +604,7 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
     ctx->has_layout = true;
     ctx->cfg = md::default_cfg(ctx);
     ctx->tuned = false;
-    return md::prepare_launch(ctx);
+    return md::prepare_default(ctx);
 }
 
 md_status md_set_integrator(md_ctx *ctx, int integrator) {

@@ -68,3 +68,35 @@ dev = ctypes.c_int(-1)
 fake.hipGetDevice(ctypes.byref(dev))
 assert dev.value == 0  # the caller's device again
 """)
+
+
+LAYOUTS = {"eight_lanes": "[32] * 20", "four_lanes": "[8, 5, 2] * 900", "one_lane": "[32] * 2000",
+           "blocks": "[160, 31, 7]", "single": "[1] * 300"}
+SETTERS = {
+    "wind": "md.md_set_wind(c, models=md.MD_WIND_CONSTANT, v_mean=(0.1, 0.0, 0.0))",
+    "wind_off": "md.md_set_wind(c, models=0)",
+    "rk4": "md.md_set_integrator(c, md.MD_INTEG_RK4)",
+    "euler": "md.md_set_integrator(c, md.MD_INTEG_EULER)",
+    "dr": "d = md.md_dr(4096, None, None, 0.0, 0.0, 0.0, 0.0, 1, None, None)\n"
+          "md.check(md.lib().md_set_domain_randomization(c, ctypes.byref(d)), c)",
+    "dr_off": "md.md_set_domain_randomization(c, None)",
+}
+
+
+@pytest.mark.parametrize("name", list(LAYOUTS))
+@pytest.mark.parametrize("first", ["", "wind", "rk4", "dr"])
+def test_no_call_after_binding_allocates(fake, name, first):
+    """Whatever is switched on or off after binding, a step (which a caller may
+    be capturing) finds its tables: no allocation and no copy."""
+    off = {"": "", "wind": "wind_off", "rk4": "euler", "dr": "dr_off"}
+    code = "c = md.md_create(md.md_default_params_cf2x(), 1 / 240, 7, md.MD_ACT_PID, 1)\n"
+    code += SETTERS.get(first, "") + "\n"
+    code += "md.md_bind_layout(c, np.concatenate([[0], np.cumsum(%s)]).astype(np.int32))\nlog()\n" % LAYOUTS[name]
+    for s in ("", off[first], "wind", "wind_off", "rk4", "euler", "dr", "dr_off"):
+        code += SETTERS.get(s, "") + """
+step(c)
+md.md_datagen(c, state(), 7, T(), T(), stream=0)
+calls = log()
+assert sum("launch" in l for l in calls) == 2 and len(calls) == 2, (%r, calls)
+""" % s
+    fake(code)
