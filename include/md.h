@@ -168,8 +168,9 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
  * do not depend on how environments are packed or on how a rollout is split
  * into launches (exception: with dw_dz_min 0, drones whose heights differ by
  * less than 5.4e-20 m but not by 0, where the model's 1/dz^2 leaves the range
- * of float32 and a partner outside the wake adds a NaN or nothing).  The configuration that binding a layout gives may run a small
- * layout with 4 or 8 lanes per drone in that same ascending order.  Errors: MD_E_LAYOUT if no
+ * of float32 and a partner outside the wake adds a NaN or nothing).  The configuration that binding a layout gives runs a small
+ * layout with 4 or 8 lanes per drone in that same ascending order, also where
+ * it is set or chosen by the autotuner.  Errors: MD_E_LAYOUT if no
  * layout is bound, MD_E_INVALID_ARG for null required pointers or
  * n_steps < 0. */
 md_status md_step(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,

@@ -306,9 +306,8 @@ void free_bins(md_ctx *ctx) {
 
 // How a configuration is launched: which bins, and the library's own sweeps in
 // place of the one-lane all-pairs one where they are the better way to the
-// same sums.  `choose`: the configuration is the layout's default and not the
-// caller's choice; `plain`: the Euler step without wind or randomisation.
-static LaunchPlan plan_of(const md_ctx *ctx, const LaunchCfg &cfg, bool choose, bool plain) {
+// same sums.  `plain`: the Euler step without wind or randomisation.
+static LaunchPlan plan_of(const md_ctx *ctx, const LaunchCfg &cfg, bool plain) {
     LaunchPlan p{cfg, 64 * cfg.waves, BIN_PACKED};
     if (!(ctx->mask & MD_AERO_DW)) return p;
     p.slots = 64 * cfg.waves / cfg.lpd;
@@ -322,8 +321,9 @@ static LaunchPlan plan_of(const md_ctx *ctx, const LaunchCfg &cfg, bool choose, 
         // bin stays idle behind it
         const int w = (ctx->max_m + 63) / 64;
         p.slots = 64 * w * std::max(1, cfg.waves / w);
-    } else if (choose && plain && ctx->max_m > 1) {
-        // Several lanes per drone where one each would leave SIMDs without a
+    } else if (plain && ctx->max_m > 1 && cfg == default_cfg(ctx)) {
+        // The layout's default configuration (bound, set or tuned alike):
+        // several lanes per drone where one each would leave SIMDs without a
         // wave (a wave per SIMD is 65536 lanes).  Measured, us per 100 steps
         // with 1 / 4 / 8 lanes: M = 32, 8192 drones 221 / 129 / 100, 16384
         // drones 222 / 128 / 129, 32768 drones 230 / 163 / 202, 65536 drones
@@ -342,8 +342,8 @@ static LaunchPlan plan_of(const md_ctx *ctx, const LaunchCfg &cfg, bool choose, 
     return p;
 }
 
-LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose) {
-    return plan_of(ctx, cfg, choose, ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models);
+LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg) {
+    return plan_of(ctx, cfg, ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models);
 }
 
 LaunchCfg default_cfg(const md_ctx *ctx) {
@@ -364,7 +364,7 @@ md_status prepare_launch(md_ctx *ctx) {
         while (64 * waves < ctx->max_m) waves *= 2;
         return build_bins(ctx, 64 * waves, BIN_PACKED, &bs);
     }
-    const LaunchPlan p = plan_for(ctx, ctx->cfg, !ctx->tuned);
+    const LaunchPlan p = plan_for(ctx, ctx->cfg);
     return build_bins(ctx, p.slots, p.mode, &bs);
 }
 
@@ -376,7 +376,7 @@ static md_status prepare_default(md_ctx *ctx) {
     BinSet *bs = nullptr;
     md_status rc = build_bins(ctx, 64 * ctx->cfg.waves, BIN_PACKED, &bs);
     for (bool plain : {false, true}) {
-        const LaunchPlan p = plan_of(ctx, ctx->cfg, true, plain);
+        const LaunchPlan p = plan_of(ctx, ctx->cfg, plain);
         if (rc == MD_OK) rc = build_bins(ctx, p.slots, p.mode, &bs);
     }
     return rc;
@@ -394,9 +394,9 @@ static hipError_t launch_act(const md_ctx *ctx, const StepArgs &a, const LaunchC
 
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,
-                 const LaunchCfg &cfg, bool choose) {
+                 const LaunchCfg &cfg) {
     BinSet *bs = nullptr;
-    const LaunchPlan plan = plan_for(ctx, cfg, choose);
+    const LaunchPlan plan = plan_for(ctx, cfg);
     md_status rc = build_bins(ctx, plan.slots, plan.mode, &bs);
     if (rc != MD_OK) return rc;
     StepArgs a;
@@ -603,7 +603,6 @@ md_status md_bind_layout(md_ctx *ctx, const int32_t *h_env_offsets, int n_envs, 
     }
     ctx->has_layout = true;
     ctx->cfg = md::default_cfg(ctx);
-    ctx->tuned = false;
     return md::prepare_default(ctx);
 }
 
@@ -623,7 +622,6 @@ md_status md_set_integrator(md_ctx *ctx, int integrator) {
     if (ctx->has_layout && !md::cfg_valid(ctx, ctx->cfg)) {
         // the Runge-Kutta kernel sweeps neighbours with one lane per drone
         ctx->cfg = md::default_cfg(ctx);
-        ctx->tuned = false;
     }
     return MD_OK;
 }
@@ -670,7 +668,6 @@ md_status md_set_domain_randomization(md_ctx *ctx, const md_dr *dr) {
     if (ctx->has_layout && !md::cfg_valid(ctx, ctx->cfg)) {
         // workgroups of the randomised step hold at most MAX_THREADS_DR threads
         ctx->cfg = md::default_cfg(ctx);
-        ctx->tuned = false;
     }
     return MD_OK;
 }
@@ -753,7 +750,7 @@ md_status md_step(md_ctx *ctx, const md_state *s, const float *d_action, int act
                                                                  n_obs_slots, n_steps, step0,
                                                                  (hipStream_t)stream);
     return md::launch(ctx, s, d_action, action_per_step, d_obs, n_obs_slots, n_steps, step0,
-                      (hipStream_t)stream, ctx->cfg, !ctx->tuned);
+                      (hipStream_t)stream, ctx->cfg);
 }
 
 }  // extern "C"

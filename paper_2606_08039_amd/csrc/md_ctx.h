@@ -54,7 +54,6 @@ struct md_ctx {
     int uniform_m = 0;  // the common size of all non-empty environments, or 0
     std::map<int, md::BinSet> binsets;  // keyed by 4 x slots per bin + packing mode (BinMode)
     md::LaunchCfg cfg{1, 4, 1, 0};
-    bool tuned = false;
     // optional subsystems
     md::SurrogateState *sur = nullptr;
     std::string err;
@@ -84,11 +83,11 @@ struct LaunchPlan {
     LaunchCfg how;
     int slots, mode;
 };
-LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg, bool choose);
+LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg);
 LaunchCfg default_cfg(const md_ctx *ctx);
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,
-                 const LaunchCfg &cfg, bool choose);
+                 const LaunchCfg &cfg);
 
 // Build the bin tables the next md_step will use (synchronous uploads).
 md_status prepare_launch(md_ctx *ctx);

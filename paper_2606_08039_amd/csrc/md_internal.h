@@ -133,6 +133,9 @@ struct LaunchCfg {
     int sym;     // pair-symmetric sweep (lpd must be 1): 1 LDS term matrix, 2 wave permutes,
                  // 3 whole-wave rotation on interleaved uniform bins; inside the library also
                  // SWEEP_BLOCK and SWEEP_LANES
+    bool operator==(const LaunchCfg &o) const {
+        return lpd == o.lpd && unroll == o.unroll && waves == o.waves && sym == o.sym;
+    }
 };
 
 // The one-lane all-pairs configuration (lpd 1, sym 0) sweeps environments of

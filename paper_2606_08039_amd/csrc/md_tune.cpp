@@ -35,9 +35,12 @@ static std::string signature(const md_ctx *ctx) {
         h ^= (uint64_t)(ctx->off[e + 1] - ctx->off[e]);
         h *= 1099511628211ull;
     }
+    // (choices for layouts whose default has several lanes per drone, cached
+    // when that was no candidate, are measured again)
+    const bool lanes = plan_for(ctx, default_cfg(ctx)).how.sym == SWEEP_LANES;
     char buf[176];
-    std::snprintf(buf, sizeof buf, "n%d_e%d_m%d_h%016llx_mask%u_act%d_int%d", ctx->n_drones, ctx->n_envs,
-                  ctx->max_m, (unsigned long long)h, ctx->mask, ctx->act, ctx->integ);
+    std::snprintf(buf, sizeof buf, "n%d_e%d_m%d_h%016llx_mask%u_act%d_int%d%s", ctx->n_drones, ctx->n_envs,
+                  ctx->max_m, (unsigned long long)h, ctx->mask, ctx->act, ctx->integ, lanes ? "_lanes" : "");
     return buf;
 }
 
@@ -148,10 +151,8 @@ static void cache_store(const std::string &path, const std::string &sig, const L
 
 // A new launch configuration makes the captured rollouts stale.
 static void set_cfg(md_ctx *ctx, const LaunchCfg &c) {
-    const LaunchCfg &o = ctx->cfg;
-    if (o.lpd != c.lpd || o.unroll != c.unroll || o.waves != c.waves || o.sym != c.sym) invalidate_graphs(ctx);
+    if (!(ctx->cfg == c)) invalidate_graphs(ctx);
     ctx->cfg = c;
-    ctx->tuned = true;
 }
 
 md_status autotune(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step, float *d_obs,
@@ -165,10 +166,7 @@ md_status autotune(md_ctx *ctx, const md_state *s, const float *d_action, int ac
         return MD_OK;
     }
     const size_t N = (size_t)ctx->n_drones;
-    if (N == 0 || n_steps <= 0) {
-        ctx->tuned = true;
-        return MD_OK;
-    }
+    if (N == 0 || n_steps <= 0) return MD_OK;
     // scratch copies of the state: the caller's state is never advanced
     const bool dr = ctx->dr_on, ring = dr && ctx->dr.delay != nullptr;
     const bool oring = dr && ctx->dr.obs_delay != nullptr;
@@ -231,7 +229,7 @@ md_status autotune(md_ctx *ctx, const md_state *s, const float *d_action, int ac
     auto timed = [&](const LaunchCfg &c, float &ms) {
         e = hipEventRecord(a, st);
         if (e != hipSuccess) return;
-        rc = launch(ctx, &ws, d_action, action_per_step, d_obs, d_obs ? n_obs_slots : 0, n_steps, step0, st, c, false);
+        rc = launch(ctx, &ws, d_action, action_per_step, d_obs, d_obs ? n_obs_slots : 0, n_steps, step0, st, c);
         if (rc != MD_OK) return;
         e = hipEventRecord(b, st);
         if (e == hipSuccess) e = hipEventSynchronize(b);
@@ -321,10 +319,7 @@ md_status md_autotune(md_ctx *ctx, const md_state *s, const float *d_action, int
         ctx->err = "md_autotune: null state or action, or negative n_steps / step0";
         return MD_E_INVALID_ARG;
     }
-    if (ctx->mask & MD_AERO_SURROGATE) {
-        ctx->tuned = true;  // the surrogate kernel has one configuration
-        return MD_OK;
-    }
+    if (ctx->mask & MD_AERO_SURROGATE) return MD_OK;  // the surrogate kernel has one configuration
     return md::autotune(ctx, s, d_action, action_per_step, nullptr, 0, n_steps, step0, (hipStream_t)stream,
                         cache_path, force);
 }
@@ -342,10 +337,7 @@ md_status md_autotune_obs(md_ctx *ctx, const md_state *s, const float *d_action,
                    "n_steps / step0";
         return MD_E_INVALID_ARG;
     }
-    if (ctx->mask & MD_AERO_SURROGATE) {
-        ctx->tuned = true;  // the surrogate kernel has one configuration
-        return MD_OK;
-    }
+    if (ctx->mask & MD_AERO_SURROGATE) return MD_OK;  // the surrogate kernel has one configuration
     return md::autotune(ctx, s, d_action, action_per_step, d_obs, n_obs_slots, n_steps, step0, (hipStream_t)stream,
                         cache_path, force);
 }

@@ -37,6 +37,27 @@ def context(sizes, act=None, mask=7):
     md.md_bind_layout(c, np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
     return c
 
+def kernels(lines):
+    return [l.split()[2] for l in lines if "launch" in l]
+
+LANES = ("ELi4ELi1ELi5", "ELi8ELi1ELi5")  # the step kernel's template arguments: lanes, unroll, sweep
+
+def lanes(names):
+    return [any(x in n for x in LANES) for n in names]
+
+# a clock for the tuner: launches of several lanes take `fast`, others `slow`
+CLOCK = ctypes.CFUNCTYPE(ctypes.c_float)
+def clock(fast, slow):
+    def ms():
+        return fast if lanes([kernels(log(False))[-1]])[0] else slow
+    f = CLOCK(ms)
+    fake.fake_clock(f)
+    return f
+
+def tune(c, cache="", n_steps=10):
+    ms = state()
+    md.check(md.lib().md_autotune(c, ctypes.byref(ms), 4096, 0, n_steps, 0, 0, cache.encode(), 0), c)
+
 def step(c, n=1, obs=None):
     md.md_step(c, state(), T(), False, obs, 1 if obs is not None else 0, n, 0, stream=0)
 """
@@ -100,3 +121,69 @@ calls = log()
 assert sum("launch" in l for l in calls) == 2 and len(calls) == 2, (%r, calls)
 """ % s
     fake(code)
+
+
+def test_the_tuner_measures_the_default_plan_and_may_keep_it(fake, tmp_path):
+    cache = str(tmp_path / "tune.json")
+    fake("""
+c = context([32] * 20)
+cfg = md.md_get_launch_config(c)
+keep = clock(1.0, 2.0)
+tune(c, %r)
+seen = lanes(kernels(log()))
+assert any(seen) and not all(seen)
+step(c)
+assert lanes(kernels(log())) == [True]
+assert md.md_get_launch_config(c) == cfg
+# another context takes the cached choice
+d = context([32] * 20)
+md.md_set_launch_config(d, lanes_per_drone=1, unroll=1, waves_per_group=1)
+log()
+tune(d, %r)
+assert not kernels(log())
+step(d)
+assert lanes(kernels(log())) == [True]
+# and where another is faster, that one
+keep = clock(2.0, 1.0)
+tune(c)
+log()
+step(c)
+assert lanes(kernels(log())) == [False]
+""" % (cache, cache))
+
+
+def test_a_choice_cached_before_the_default_had_lanes_is_measured_again(fake, tmp_path):
+    cache = str(tmp_path / "tune.json")
+    fake("""
+import json
+c = context([32] * 20)
+keep = clock(1.0, 2.0)
+tune(c, %r)
+rec = json.load(open(%r))
+old = dict(rec[0], lpd=4, unroll=1, waves=2, sym=0)
+old["sig"] = old["sig"].replace("_lanes", "")
+assert old["sig"] != rec[0]["sig"]
+open(%r, "w").write("[\\n" + json.dumps(old) + "\\n]\\n")
+d = context([32] * 20)
+log()
+tune(d, %r)
+assert kernels(log())
+step(d)
+assert lanes(kernels(log())) == [True]
+""" % ((cache,) * 4))
+
+
+def test_the_default_configuration_set_or_kept_stays_the_default(fake):
+    fake("""
+for sizes in ([32] * 20, [8, 5, 2] * 900):
+    c = context(sizes)
+    md.md_set_launch_config(c, **md.md_get_launch_config(c))
+    tune(c, n_steps=0)
+    log()
+    step(c)
+    assert lanes(kernels(log())) == [True]
+    # another unroll is the caller's own one-lane configuration
+    md.md_set_launch_config(c, lanes_per_drone=1, unroll=2, waves_per_group=1)
+    step(c)
+    assert lanes(kernels(log())) == [False]
+""")
