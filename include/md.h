@@ -326,8 +326,9 @@ typedef struct md_launch_config {
     int lanes_per_drone; /* 1, 2 or 4 lanes share one drone's neighbour sweep */
     int unroll;          /* neighbour-loop unroll: 1, 2 or 4 (1 for pair_symmetric 2 and 3) */
     int waves_per_group; /* 1, 2, 4, 8 or 16 wave64s per workgroup (bin of 64*w/lpd slots); with
-                            pair_symmetric 3 a launch that is short, stores no rows or does not
-                            fill the GPU runs every wave as a workgroup of its own */
+                            pair_symmetric 3 an upper bound: only long launches that store rows
+                            and fill the GPU evenly run in groups (of 16 waves, Runge-Kutta
+                            8), the others run every wave as a workgroup of its own */
     int pair_symmetric;  /* 0: all ordered pairs (one lane per drone and environments of more
                             than 112 drones: each unordered pair once, block by block); 1: each
                             unordered pair once, terms routed through an LDS matrix; 2: each unordered pair once, terms routed

@@ -346,6 +346,59 @@ LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg) {
     return plan_of(ctx, cfg, ctx->integ == MD_INTEG_EULER && !ctx->dr_on && !ctx->wind.models);
 }
 
+// Waves of the rotation sweep's workgroups, at most the configured ones.  Its
+// waves are independent, and one-wave workgroups suit most launches: no CU
+// waits for a whole group's end, and waves that evaluate unequal numbers of
+// tested pairs run on.  Groups pay where a launch is long and stores rows: their
+// waves start every step together and write the same rows together, where
+// waves of their own drift apart.  Measured, ms, one wave / groups of 8 / of 16,
+// rows stored, environments of 32:
+//   Euler 8192 envs, 250 steps 1.19 / 1.21 / 1.21, 500 2.41 / 2.47 / 2.45, 1000
+//   5.10 / 5.07 / 4.87; 6500 envs, 500 2.21 / 2.25 / 2.20, 1000 4.82 / 4.66 /
+//   4.26; 16384 envs, 1000 9.91 / 9.93 / 9.84; of 64: 4096 envs, 250 steps 1.13 /
+//   1.18 / 1.18, 500 2.28 / 2.31 / 2.20, 750 3.50 / 3.46 / 3.25; of 16: 16384
+//   envs, 375 steps 1.59 / 1.67 / 1.50, 750 3.22 / 3.34 / 2.98
+//   wind 8192 envs, 250 steps 1.66 / 1.66 / 1.64, 500 3.53 / 3.57 / 3.42, 1000
+//   7.32 / 7.23 / 6.73; 6500 envs, 500 3.34 / 3.42 / 3.23
+//   Runge-Kutta 8192 envs, 60 steps 0.84 / 0.88 / 0.93, 500 7.90 / 7.44 / 7.65,
+//   1000 15.6 / 14.8 / 15.3; 6500 envs, 1000 15.2 / 14.5 / 15.2; of 16: 16384
+//   envs, 1000 10.4 / 10.6 / 10.3
+//   randomised 4096 envs, 250 steps 3.0 / 3.3, 8192 6.1 / 6.1, 12000 8.7 / 9.2
+// Without rows the two differ by 2 % at most, randomised by 10 % for one wave.
+// Where a group's granularity puts more waves on a SIMD than waves of their own
+// would (12000 envs in groups of 16: 8 instead of 6), or SIMDs hold fewer than
+// four, groups lose up to 40 %.
+//
+// Tests (md_sweep.h) of up to 32 drones whose rows are stored pay where four or
+// more waves of their own share a SIMD, as do those without rows.  With ->
+// without tests: fewer waves, Euler 2048 envs, 60 / 500 steps 179 / 1396 -> 165 /
+// 1251 us, 4096 envs 191 / 1583 -> 176 / 1455 us, 5000 envs, 500 steps 1839 -> 1754
+// us, wind 4096 envs, 500 steps 2.05 -> 1.93 ms; four, 8192 envs at a pitch of
+// 1.25-1.6 m, 60 steps 288 -> 299 us, at 1 m 298 -> 292 us; groups of 16, 1000
+// steps 5.28 -> 4.87 ms, wind 6.73 -> 6.60 ms.
+constexpr int WAVES_FULL = 4;  // per SIMD
+
+static long long rotation_waves_per_simd(const md_ctx *ctx, int group) {
+    auto blocks = [](long long n, long long size) { return (n + size - 1) / size; };
+    const long long all = blocks(ctx->n_drones, 64);
+    return group == 1 ? blocks(all, 4 * ctx->n_cu) : blocks(blocks(all, group), ctx->n_cu) * (group / 4);
+}
+
+static int rotation_waves(const md_ctx *ctx, int waves, bool rows, int n_steps) {
+    constexpr int LONG = 500;
+    const bool rk4 = ctx->integ == MD_INTEG_RK4;
+    const int group = rk4 ? 8 : 16;
+    if (waves < group || !rows || n_steps < LONG || ctx->dr_on || (rk4 && ctx->max_m < 32)) return 1;
+    const long long apart = rotation_waves_per_simd(ctx, 1);
+    return apart >= WAVES_FULL && rotation_waves_per_simd(ctx, group) <= apart ? group : 1;
+}
+
+static bool rotation_tested(const md_ctx *ctx, int waves, bool rows) {
+    if (ctx->max_m > 32 || !rows || ctx->dr_on) return true;
+    if (ctx->integ == MD_INTEG_RK4) return waves == 1;
+    return waves == 1 && rotation_waves_per_simd(ctx, 1) >= WAVES_FULL;
+}
+
 LaunchCfg default_cfg(const md_ctx *ctx) {
     LaunchCfg c{1, 4, 1, 0};
     const int max_waves = ctx->dr_on ? MAX_THREADS_DR / 64 : 16;
@@ -414,7 +467,12 @@ md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int acti
     a.N = ctx->n_drones;
     a.bins = BinTables{bs->d_slot, bs->d_mmax};
     a.tstride = pair_stride(ctx->max_m);
-    const LaunchCfg &how = plan.how;
+    LaunchCfg how = plan.how;
+    a.untested = 0;
+    if (how.sym == 3) {
+        how.waves = rotation_waves(ctx, how.waves, a.obs != nullptr, n_steps);
+        a.untested = rotation_tested(ctx, how.waves, a.obs != nullptr) ? 0 : 1 << 30;
+    }
     hipError_t e = hipSuccess;
     switch (ctx->act) {
         case 0: e = launch_act<0>(ctx, a, how, *bs, st); break;

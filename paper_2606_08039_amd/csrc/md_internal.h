@@ -95,26 +95,8 @@ struct StepArgs {
     int tstride;  // row stride (floats) of the pair-term matrix in LDS (sym sweep)
     DrPtr dr;       // domain randomisation (used by the disturbed instantiation only)
     WindArgs wind;  // wind (disturbed instantiation only)
+    int untested;   // sweeps that the rotation first makes without tests
 };
-
-// Threads of the rotation sweep's workgroups.  Its waves are independent, and
-// one-wave workgroups suit launches that leave CUs idle (16384 x 8 drones, 100
-// steps: 243 us, in groups of 8 and 16 waves 310 and 528 us) and waves that
-// evaluate unequal numbers of tested pairs.  Long launches that store rows and
-// fill the chip take the configured groups, and up to 32 drones no tests:
-// their waves keep step and write the same rows together, where waves of their
-// own drift apart over the steps (8192 x 32 with every row, one wave with
-// tests against 16 waves without: 60 steps 274 and 293 us, 500 steps 2.28 and
-// 2.35 ms, 1000 steps 4.95 and 4.74 ms; Runge-Kutta 50 steps 593 and 779 us,
-// 1000 steps 15.5 and 14.4 ms).  The kernels with wind or randomisation take
-// the configured groups wherever they fill the chip (wind, 1000 steps: 6.3 ms
-// in waves, 6.1 ms in groups).
-constexpr int ROT_LONG = 750;
-inline int rot_threads(const StepArgs &a, int n_bins, int threads, bool plain) {
-    const bool fills = (long long)n_bins * threads >= 256 * 1024;
-    const bool grouped = fills && (!plain || (a.obs != nullptr && a.n_steps >= ROT_LONG && a.tstride <= 32));
-    return grouped ? threads : 64;
-}
 
 // Row stride (floats) of the pair-term matrix of the pair-symmetric sweep: a
 // multiple of 4 (rows are summed with 16-byte LDS reads) that holds the

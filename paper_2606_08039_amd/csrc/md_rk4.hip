@@ -32,7 +32,8 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
     const bool valid = di >= 0;
     const int lo = tab.y >> 16;
     const int menv = tab.y & 0xffff;
-    // each wave of the rotation sweep is a workgroup of its own (md_step_kernel.h)
+    // (the rotation sweep's workgroups may be smaller than its bins, which all
+    // report the same M)
     const int mm_word = a.bins.bin_mmax[SYM == 3 ? 0 : blockIdx.x];
     if (SYM == 3 && blockDim.x == 64 && __ballot(valid) == 0ull) return;
     const int mmax = mm_word & 0xffff;
@@ -84,7 +85,7 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
     int phase = (ACT >= 1) ? (int)(a.step0 % (long long)c.decim) : 0;
     int oslot = 0;
     SweepMemo memo;
-    if (SYM == 3 && blockDim.x > 64 && mmax <= 32) memo.dense = 1 << 30;  // (see rot_threads)
+    if (SYM == 3) memo.dense = a.untested;
     // One body for the four stages where a sweep fills it: unrolled, the
     // rotation's five sizes took 84 KB of code and the block sweep spilled (50
     // steps, unrolled -> one body: 4096 x 32 drones 467 -> 420 us).  The sweeps
@@ -263,7 +264,7 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, SWEEP_BLOCK>), dim3(n_bins), dim3(threads), lds, st, a);
             else if (cfg.sym == 3) {
-                const int wg = rot_threads(a, n_bins, threads, true);
+                const int wg = 64 * cfg.waves;  // (a part of the bin)
                 hipLaunchKernelGGL((rk4_kernel<MASK, ACT, 1, 3>), dim3(n_bins * threads / wg),
                                    dim3(wg), lds * wg / threads, st, a);
             } else

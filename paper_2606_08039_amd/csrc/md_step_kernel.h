@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(DIST == 2 ? MAX_THREADS_DR : 1024) step_kernel
     bool motor_due = true;  // uniform
     float T = 0.f, tx = 0.f, ty = 0.f, tz = 0.f;
     SweepMemo memo;
-    if (seg_on && blockDim.x > 64 && mmax <= 32) memo.dense = 1 << 30;  // (see rot_threads)
+    if (SYM == 3) memo.dense = a.untested;
     for (int step = 0; step < a.n_steps; ++step) {
         float4 *buf = lds_pos + (step & 1) * (2 * slots);
         if (MASK & 4u) {
@@ -679,7 +679,7 @@ hipError_t launch_l(const StepArgs &a, const LaunchCfg &cfg, int n_bins, int thr
             if (cfg.sym == SWEEP_BLOCK)
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, SWEEP_BLOCK, DIST>), dim3(n_bins), dim3(threads), lds, st, a);
             else if (cfg.sym == 3) {
-                const int wg = rot_threads(a, n_bins, threads, DIST == 0);
+                const int wg = 64 * cfg.waves;  // (a part of the bin)
                 hipLaunchKernelGGL((step_kernel<MASK, ACT, 1, 1, 3, DIST>), dim3(n_bins * threads / wg),
                                    dim3(wg), lds * wg / threads, st, a);
             } else

@@ -187,3 +187,38 @@ for sizes in ([32] * 20, [8, 5, 2] * 900):
     step(c)
     assert lanes(kernels(log())) == [False]
 """)
+
+
+def test_groups_of_the_rotation_sweep(fake):
+    """One wave per workgroup unless the launch is long, stores rows and fills
+    the 256 CUs evenly; never more threads than the configuration names, and
+    every wave of the bins is launched."""
+    fake("""
+WIND, RK4, DR = "wind", "rk4", "dr"
+def blocks(envs, m, steps, waves, what=None, rows=True):
+    c = context([m] * envs)
+    if what == WIND:
+        md.md_set_wind(c, models=md.MD_WIND_CONSTANT, v_mean=(0.1, 0.0, 0.0))
+    if what == RK4:
+        md.md_set_integrator(c, md.MD_INTEG_RK4)
+    if what == DR:
+        d = md.md_dr(4096, None, None, 0.0, 0.0, 0.0, 0.0, 1, None, None)
+        md.check(md.lib().md_set_domain_randomization(c, ctypes.byref(d)), c)
+    md.md_set_launch_config(c, lanes_per_drone=1, unroll=1, waves_per_group=waves, pair_symmetric=3)
+    log()
+    step(c, steps, T() if rows else None)
+    grid, block = [int(x) for x in [l for l in log() if "launch" in l][0].split()[3:5]]
+    need = -(-envs * m // 64)
+    assert need * 64 <= grid * block < (need + waves) * 64, (grid, block)
+    md.md_destroy(c)
+    return block // 64
+for args, want in [((8192, 32, 500, 16), 16), ((8192, 32, 499, 16), 1), ((8192, 32, 500, 8), 1),
+                   ((8192, 32, 500, 16, None, False), 1), ((6500, 32, 1000, 16), 16), ((6144, 32, 1000, 16), 1),
+                   ((6146, 32, 1000, 16), 16), ((8193, 32, 1000, 16), 1), ((12000, 32, 1000, 16), 1),
+                   ((16384, 32, 1000, 16), 16), ((4096, 64, 1000, 16), 16), ((16384, 16, 1000, 16), 16),
+                   ((100, 32, 1000, 16), 1), ((8192, 32, 1000, 16, WIND), 16), ((8192, 32, 1000, 8, DR), 1),
+                   ((8192, 32, 500, 16, RK4), 8), ((8192, 32, 500, 8, RK4), 8), ((8192, 32, 500, 4, RK4), 1),
+                   ((12000, 32, 500, 16, RK4), 8), ((10000, 32, 500, 16, RK4), 1), ((16384, 16, 500, 16, RK4), 1)]:
+    got = blocks(*args)
+    assert got == want, (args, got, want)
+""")
