@@ -435,6 +435,14 @@ static md_status prepare_default(md_ctx *ctx) {
     return rc;
 }
 
+bool same_launch(const md_ctx *ctx, const LaunchCfg &x, const LaunchCfg &y, bool rows, int n_steps) {
+    const LaunchPlan p = plan_for(ctx, x), q = plan_for(ctx, y);
+    if (p.how.sym != q.how.sym || p.how.lpd != q.how.lpd || p.how.unroll != q.how.unroll) return false;
+    if (p.how.sym == 3)  // (one order of the waves, whatever the bins)
+        return rotation_waves(ctx, p.how.waves, rows, n_steps) == rotation_waves(ctx, q.how.waves, rows, n_steps);
+    return p.slots == q.slots && p.mode == q.mode;
+}
+
 // The step kernel of the context's integrator and disturbances.
 template <int ACT>
 static hipError_t launch_act(const md_ctx *ctx, const StepArgs &a, const LaunchCfg &cfg, const BinSet &bs,

@@ -84,6 +84,8 @@ struct LaunchPlan {
     int slots, mode;
 };
 LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg);
+// Whether two configurations run the same kernel on the same workgroups.
+bool same_launch(const md_ctx *ctx, const LaunchCfg &x, const LaunchCfg &y, bool rows, int n_steps);
 LaunchCfg default_cfg(const md_ctx *ctx);
 md_status launch(md_ctx *ctx, const md_state *s, const float *d_action, int action_per_step,
                  float *d_obs, int n_obs_slots, int n_steps, int64_t step0, hipStream_t st,

@@ -71,12 +71,25 @@ bool cfg_valid(const md_ctx *ctx, const LaunchCfg &c) {
     return true;
 }
 
-static std::vector<LaunchCfg> candidates(const md_ctx *ctx) {
+// Configurations that differ in what launches of this kind and length run.  Of
+// several that run the same, the default or else the one of the most waves: the
+// rotation sweep's workgroups of one wave are the same launch for every
+// configured number, which is a longer launch's upper bound.
+static std::vector<LaunchCfg> candidates(const md_ctx *ctx, bool rows, int n_steps) {
     std::vector<LaunchCfg> out;
+    const LaunchCfg own = default_cfg(ctx);
+    auto add = [&](const LaunchCfg &c) {
+        for (LaunchCfg &o : out)
+            if (same_launch(ctx, o, c, rows, n_steps)) {
+                if (!(o == own)) o = c;
+                return;
+            }
+        out.push_back(c);
+    };
     if (!(ctx->mask & MD_AERO_DW)) {
         for (int w : {1, 2, 4})
             if (64 * w >= ctx->max_m) out.push_back(LaunchCfg{1, 1, w, 0});
-        if (out.empty()) out.push_back(default_cfg(ctx));
+        if (out.empty()) out.push_back(own);
         return out;
     }
     for (int sym : {0, 1, 2, 3})
@@ -84,7 +97,7 @@ static std::vector<LaunchCfg> candidates(const md_ctx *ctx) {
             for (int w : {1, 2, 4, 8, 16})
                 for (int u : {1, 2, 4}) {
                     LaunchCfg c{lpd, u, w, sym};
-                    if (cfg_valid(ctx, c)) out.push_back(c);
+                    if (cfg_valid(ctx, c)) add(c);
                 }
     return out;
 }
@@ -223,7 +236,7 @@ md_status autotune(md_ctx *ctx, const md_state *s, const float *d_action, int ac
     // Stage 1, round robin: every repetition times each candidate once, so
     // all of them see the same drift of the clock under load; the first
     // round warms up, the score is the median of the other three.
-    const std::vector<LaunchCfg> cands = candidates(ctx);
+    const std::vector<LaunchCfg> cands = candidates(ctx, d_obs != nullptr, n_steps);
     constexpr int REPS = 4;
     std::vector<float> ms_of(cands.size() * (REPS - 1), 0.f);
     auto timed = [&](const LaunchCfg &c, float &ms) {

@@ -222,3 +222,25 @@ for args, want in [((8192, 32, 500, 16), 16), ((8192, 32, 499, 16), 1), ((8192, 
     got = blocks(*args)
     assert got == want, (args, got, want)
 """)
+
+
+def test_the_tuner_times_every_launch_once(fake):
+    """Candidates that run the same kernel on the same workgroups are one, and a
+    choice of the rotation sweep leaves longer launches their groups."""
+    fake("""
+def rotation_first():
+    f = CLOCK(lambda: 1.0 if "ELi1ELi1ELi3" in kernels(log(False))[-1] else 2.0)
+    fake.fake_clock(f)
+    return f
+for sizes in ([32] * 8192, [160, 31, 7], [2, 30, 17] * 3000, [64] * 50):
+    c = context(sizes)
+    log()
+    keep = rotation_first()
+    tune(c)
+    first = [l for l in log() if "launch" in l]
+    n = first.index(first[0], 1)  # the second round begins
+    assert len(set(first[:n])) == n and first[:n] == first[n:2 * n], (sizes[0], first[:n])
+    if sizes[0] in (32, 64):
+        got = md.md_get_launch_config(c)
+        assert got["pair_symmetric"] == 3 and got["waves_per_group"] == 16, got
+""")
