@@ -36,12 +36,18 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // (dw_margin: 7 fused operations, no transcendental, no select) and push its
 // sign into a word of bits, then evaluate only the pairs that some lane needs;
 // leaving a 0 out of a sum changes no bit of it.  Where a swarm is dense
-// enough that most pairs are needed, the tests are the dearer way: a sweep that
-// evaluated more than its limit of pairs runs the next SPARSE_RETRY - 1 steps
-// without them.  Measured without -> with the tests: 512 x 256 drones, 50
+// enough that most pairs are needed, the tests are the dearer way: a sweep
+// whose tests ask for more than its limit of pairs evaluates all of them, in
+// this step and the next SPARSE_RETRY - 1, without tests.  (Evaluated one after
+// the other in the step that found them too many, and tested again every 8
+// steps, dense swarms took up to 8 % longer than without tests at all.)
+// Measured without -> with the tests: 512 x 256 drones, 50
 // steps, block sweep 617 -> 395 us; 4096 x 64, 60 steps, rotation sweep with
 // observations 433 -> 325 us, without 377 -> 240 us; 8192 x 32, 60 steps with
-// observations 300 -> 284 us.
+// observations 300 -> 284 us.  Lattices drawn together to 0.3 of their pitch,
+// where the tests are given up: 512 x 256 946 (all pairs) -> 682 us, 2048 x 64 with
+// observations 340 -> 329 us, without 303 -> 303 us, 8192 x 32 257 -> 252 us, 4096 x
+// 32 under wind 245 -> 244 us, Runge-Kutta 2048 x 64, 40 steps 618 -> 562 us.
 // The outcomes outlast a step: the block sweep, the rotation of 64 drones and
 // the one-lane sweep of the randomised step keep them until a drone of the
 // environment (or of the wave) has moved MEMO_MOVE, with a radius that allows
@@ -50,7 +56,7 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // x 256 drones, 50 steps 394 -> 175 us, Runge-Kutta 256 x 256, 20 steps 572 ->
 // 258 us; 2048 x 64, 60 steps with observations 200 -> 167 us, without 178 ->
 // 140 us; 4096 x 32 randomised, 50 steps 333 -> 312 us.
-constexpr int SPARSE_RETRY = 8;
+constexpr int SPARSE_RETRY = 32;
 // Pairs evaluated side by side where a sweep goes by batches.
 constexpr int PAIR_BATCH = 4;
 // Smallest environment that takes tests: at 32 drones a third of the 16 shifts
@@ -189,12 +195,13 @@ __device__ __forceinline__ float dw_lanes(const KConst &c0, const float4 *buf, i
 // then each lane's set bits in ascending order.  KEEP: the outcomes are kept
 // (also of partners that may come to be above).  The gather of the set bits is a serial chain through
 // LDS, so it pays where the step around it keeps the vector ALU busy and not
-// where the sweep alone is the step (SCAN, see dw_sum).
+// where the sweep alone is the step (SCAN, see dw_sum).  Where a lane asks for
+// more than a quarter of its candidates it stops, sets memo.dense, and the
+// caller evaluates every pair.
 template <bool DZMIN, bool KEEP>
 __device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 *buf, int slots, int slot, int lo,
                                                  int mmax, int menv, const Drone &d, SweepMemo &memo) {
     float acc = 0.f;
-    int rounds = 0;
     // outcomes are kept where one word and one wave hold them all
     const bool keep = KEEP && mmax <= 32 && slots == 64;
     const float lift = KEEP ? 2.002f * MEMO_MOVE : 0.f;
@@ -229,6 +236,12 @@ __device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 
             bits &= left >= 32 ? ~0u : ~(~0u >> max(left, 0));
             if (keep) bits &= ~(0x80000000u >> ((slot - lo) & 31));  // not itself
             memo.need = bits;
+            // as many rounds as the lane with the most candidates asks for
+            if (__ballot(4 * __builtin_popcount(bits) > n) != 0ull) {
+                memo.dense = SPARSE_RETRY;
+                memo.forget();
+                return 0.f;
+            }
         }
         const KConst c = pair_consts(c0);
         while (__ballot(bits != 0u) != 0ull) {
@@ -237,12 +250,7 @@ __device__ __forceinline__ float dw_sweep_sparse(const KConst &c0, const float4 
             const float t = dw_term<DZMIN>(c, p.x - d.px, p.y - d.py, p.z - d.pz);
             acc += bits != 0u ? t : 0.f;
             bits &= ~(0x80000000u >> k);
-            ++rounds;
         }
-    }
-    if (5 * rounds > 2 * mmax) {
-        memo.dense = SPARSE_RETRY - 1;
-        memo.forget();
     }
     return acc;
 }
@@ -406,48 +414,48 @@ __device__ __forceinline__ float dw_pairs_rot(const KConst &c0, const float4 *ow
 // latencies (50 steps, serial -> batched: 8192 x 16 drones 314 -> 261 us, 4096
 // x 32 547 -> 430 us); around the Euler step it overlaps them by itself, and
 // batches would spill.
+// Environments of 64 drones go through a loop over the batches: unrolled, their
+// eight batches would take the registers of every size.
 template <bool DZMIN, int E>
 __device__ __forceinline__ float dw_pairs_rot_batched(const KConst &c0, const float4 *own, int lane,
                                                       const Drone &d) {
     constexpr int M = 64 / E;
     constexpr int H = (M - 1) / 2;
     const KConst c = pair_consts(c0);
-    // the permute addresses pa + 256 - 4 E k fold into the instructions'
-    // offset field when pa is formed inside the step: hoisted out of the
-    // step loop instead, they would hold one register per shift
-    int pa = 4 * lane;
-    asm volatile("" : "+v"(pa));
     constexpr int B = M / 2 < PAIR_BATCH ? M / 2 : PAIR_BATCH;
+    constexpr int N = (H + 1) / B;  // batches
+    // the permute addresses pa - 4 E k fold into the instructions' offset field
+    // when pa is formed inside the step: hoisted out of the step loop instead,
+    // they would hold one register per shift
+    int pa = 4 * lane + 256;
+    asm volatile("" : "+v"(pa));
     float x[B], y[B], z[B], mine[B], recv[B];
+    auto load = [&](const float4 *q) {
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-        const float4 q = own[E * (1 + u)];
-        x[u] = q.x;
-        y[u] = q.y;
-        z[u] = q.z;
-    }
+        for (int u = 0; u < B; ++u) {
+            const float4 v = q[E * u];
+            x[u] = v.x;
+            y[u] = v.y;
+            z[u] = v.z;
+        }
+    };
     float acc = 0.f;
-#pragma unroll
-    for (int k = 1; k <= H + 1; k += B) {
+    // the shifts k .. k + B - 1, q the partner's position at shift k
+    auto batch = [&](const float4 *q, int k, bool first, bool last) {
         float dz[B], d2[B], t[B];
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             dz[u] = z[u] - d.pz;
             d2[u] = dw_d2(x[u] - d.px, y[u] - d.py);
-            if (k + B <= H + 1) {
-                const float4 q = own[E * (k + B + u)];
-                x[u] = q.x;
-                y[u] = q.y;
-                z[u] = q.z;
-            }
         }
+        if (!last) load(q + E * B);
 #pragma unroll
         for (int u = 0; u < B; ++u) t[u] = dw_raw<DZMIN>(c, d2[u], fabsf(dz[u]));
 #pragma unroll
         for (int u = 0; u < B; ++u) {
             asm volatile("" : "+v"(t[u]));  // formed before the first select
         }
-        if (k > 1) {
+        if (!first) {
 #pragma unroll
             for (int u = 0; u < B; ++u) {
                 acc += mine[u];
@@ -461,12 +469,21 @@ __device__ __forceinline__ float dw_pairs_rot_batched(const KConst &c0, const fl
             // formed here, not where the serial sum reaches it: otherwise its
             // lane mask stays live across shifts and the masks spill
             asm volatile("" : "+v"(mine[u]));
-            if (k + u > H) break;
+            if (last && u == B - 1) break;
             const float theirs = (near && dz[u] < 0.f) ? t[u] : 0.f;
-            recv[u] =
-                __int_as_float(__builtin_amdgcn_ds_bpermute(pa + (256 - 4 * E * (k + u)), __float_as_int(theirs)));
+            recv[u] = __int_as_float(__builtin_amdgcn_ds_bpermute(pa - 4 * E * (k + u), __float_as_int(theirs)));
         }
         __builtin_amdgcn_sched_barrier(0);
+    };
+    load(own + E);
+    if constexpr (E == 1) {
+        batch(own + 1, 1, true, false);
+#pragma unroll 1
+        for (int b = 1; b < N - 1; ++b) batch(own + 1 + B * b, 1 + B * b, false, false);
+        batch(own + 1 + B * (N - 1), 1 + B * (N - 1), false, true);
+    } else {
+#pragma unroll
+        for (int b = 0; b < N; ++b) batch(own + E * (1 + B * b), 1 + B * b, b == 0, b == N - 1);
     }
 #pragma unroll
     for (int u = 0; u < B; ++u) {
@@ -482,11 +499,12 @@ __device__ __forceinline__ float dw_pairs_rot_batched(const KConst &c0, const fl
 // than keeping their outcomes (8192 x 32 drones, 60 steps with observations:
 // 276 us run, 284-300 us kept; 2048 x 64 178 run, 139 us kept).  The stages of
 // a Runge-Kutta step lie close together and keep them (50 steps, every pair
-// evaluated -> kept: 8192 x 32 690 -> 593 us, 4096 x 32 421 -> 430 us, 2048 x
-// 64 641 -> 412 us).
-template <bool DZMIN, int E, bool KEEP, class Seg>
-__device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const float4 *own, int lane, bool valid,
-                                                     const Drone &d, const Seg &seg, SweepMemo &memo) {
+// evaluated -> kept: 8192 x 32 690 -> 593 us, 4096 x 32 421 -> 418 us, 2048 x
+// 64 641 -> 415 us).
+// dw_rot_tests: the needed shifts, shift k in bit 32 - k.
+template <bool DZMIN, int E, bool KEEP>
+__device__ __forceinline__ uint32_t dw_rot_tests(const KConst &c0, const float4 *own, bool valid, const Drone &d,
+                                                 SweepMemo &memo) {
     constexpr int M = 64 / E;
     constexpr int H = (M - 1) / 2;
     uint32_t need = memo.need;
@@ -498,19 +516,22 @@ __device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const flo
             const float4 q = own[E * k];
             bits = push_sign(bits, dw_margin<DZMIN, KEEP>(c, q.x - d.px, q.y - d.py, fabsf(q.z - d.pz)));
         }
-        need = wave_or(valid ? bits : 0u) << (31 - H);  // shift k in bit 32 - k
+        need = wave_or(valid ? bits : 0u) << (31 - H);
         if (KEEP) {
             memo.need = need;
             memo.stand(d);
         }
     }
-    need = (uint32_t)__builtin_amdgcn_readfirstlane((int)need);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)need);
+}
+
+template <bool DZMIN, int E, class Seg>
+__device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, uint32_t need, const float4 *own, int lane,
+                                                     const Drone &d, const Seg &seg) {
+    constexpr int M = 64 / E;
+    constexpr int H = (M - 1) / 2;
     const bool half = (need >> (31 - H)) & 1u;
     need &= ~(1u << (31 - H));
-    if (__builtin_popcount(need) > H / 2) {
-        memo.dense = SPARSE_RETRY - 1;
-        if (KEEP) memo.forget();
-    }
     const KConst c = pair_consts(c0);
     float acc = 0.f;
     seg.all();
@@ -538,12 +559,19 @@ __device__ __forceinline__ float dw_pairs_rot_sparse(const KConst &c0, const flo
 template <bool DZMIN, int E, int TESTS, bool BATCHED, class Seg>
 __device__ __forceinline__ float dw_rot_size(const KConst &c, const float4 *own, int lane, bool valid, const Drone &d,
                                              const Seg &seg, SweepMemo &memo) {
+    constexpr int H = (64 / E - 1) / 2;
     if (64 / E >= TESTS) {
-        if (__builtin_amdgcn_readfirstlane(memo.dense) == 0)
-            return dw_pairs_rot_sparse<DZMIN, E, E == 1 || BATCHED>(c, own, lane, valid, d, seg, memo);
+        if (__builtin_amdgcn_readfirstlane(memo.dense) == 0) {
+            constexpr bool KEEP = E == 1 || BATCHED;
+            const uint32_t need = dw_rot_tests<DZMIN, E, KEEP>(c, own, valid, d, memo);
+            if (__builtin_popcount(need >> (32 - H)) <= H / 2)
+                return dw_pairs_rot_sparse<DZMIN, E>(c, need, own, lane, d, seg);
+            memo.dense = SPARSE_RETRY;
+            if (KEEP) memo.forget();
+        }
         --memo.dense;
     }
-    if constexpr (BATCHED && E > 1) return dw_pairs_rot_batched<DZMIN, E>(c, own, lane, d);
+    if constexpr (BATCHED) return dw_pairs_rot_batched<DZMIN, E>(c, own, lane, d);
     return dw_pairs_rot<DZMIN, E>(c, own, lane, d, seg);
 }
 
@@ -841,15 +869,18 @@ __device__ __forceinline__ float dw_sum(const KConst &c, const float4 *buf, floa
             acc += t.z;
             acc += t.w;
         }
-    } else if (SCAN && LPD == 1 && mmax >= SPARSE_MIN_ENV && __builtin_amdgcn_readfirstlane(memo.dense) == 0) {
-        acc = c.dz_min > 0.f ? dw_sweep_sparse<true, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo)
-                             : dw_sweep_sparse<false, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo);
-    } else if (c.dz_min > 0.f) {
-        memo.dense -= SCAN && memo.dense > 0 ? 1 : 0;
-        acc = dw_sweep<true, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     } else {
-        memo.dense -= SCAN && memo.dense > 0 ? 1 : 0;
-        acc = dw_sweep<false, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
+        bool every = true;
+        if constexpr (SCAN != 0 && LPD == 1) {
+            if (mmax >= SPARSE_MIN_ENV && __builtin_amdgcn_readfirstlane(memo.dense) == 0)
+                acc = c.dz_min > 0.f ? dw_sweep_sparse<true, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo)
+                                     : dw_sweep_sparse<false, SCAN == 2>(c, buf, slots, slot, lo, mmax, menv, d, memo);
+            every = mmax < SPARSE_MIN_ENV || __builtin_amdgcn_readfirstlane(memo.dense) > 0;
+            memo.dense -= memo.dense > 0 ? 1 : 0;
+        }
+        if (every)
+            acc = c.dz_min > 0.f ? dw_sweep<true, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d)
+                                 : dw_sweep<false, LPD, UNROLL>(c, buf, lo, sub, mmax, menv, uniform, d);
     }
     // the partial sums of a drone's lanes, combined across the lanes of a
     // quad by DPP quad permutes (lane ^ 1, then lane ^ 2; every lane of the
