@@ -80,6 +80,7 @@ MD_DR_NSCALE, MD_DR_HIST, MD_DR_OBS_HIST = 14, 32, 8
 
 
 _lib = None
+_packed_step = None
 _VP = ctypes.c_void_p
 
 
@@ -107,13 +108,18 @@ def lib():
         "md_last_error": (ctypes.c_char_p, [_VP]),
         "md_bind_layout": (ctypes.c_int32, [_VP, ctypes.POINTER(ctypes.c_int32), ctypes.c_int,
                                             ctypes.c_int]),
-        "md_step": (ctypes.c_int32, [_VP, _VP, _VP, ctypes.c_int, _VP,
+        "md_step": (ctypes.c_int32, [_VP, ctypes.POINTER(md_state), _VP, ctypes.c_int, _VP,
                                      ctypes.c_int, ctypes.c_int, ctypes.c_int64, _VP]),
     }
     for name, (res, args) in sig.items():
         f = getattr(L, name)
         f.restype = res
         f.argtypes = args
+    # the same function for a DeviceState's packed pointers (a second object:
+    # callers of lib().md_step keep the check of its argument's type)
+    global _packed_step
+    _packed_step = L["md_step"]
+    _packed_step.restype, _packed_step.argtypes = ctypes.c_int32, [_VP, ctypes.c_char_p] + sig["md_step"][1][2:]
     _lib = L
     _bind_extra(L)
     return L
@@ -152,8 +158,12 @@ def _stream_ptr(stream):
         if _current_raw_stream is None:
             import torch
             torch.cuda.init()
-            raw, dev = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-            _current_raw_stream = lambda: raw(dev())  # noqa: E731
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+            dev = getattr(torch._C, "_cuda_getDevice", None)
+            if raw is None or dev is None:  # internals of torch, which another version may not have
+                _current_raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+            else:
+                _current_raw_stream = lambda: raw(dev())  # noqa: E731
         return _current_raw_stream()
     if isinstance(stream, int):
         return stream
@@ -161,13 +171,6 @@ def _stream_ptr(stream):
 
 
 _STATE_PTRS = struct.Struct("%dQ" % len(md_state._fields_))
-
-
-def _state_arg(state):
-    """What the C ABI takes for `const md_state *`: the packed pointers of a
-    DeviceState, or a reference to an md_state."""
-    return state.pointers() if hasattr(state, "pointers") else ctypes.byref(
-        state.as_md_state() if hasattr(state, "as_md_state") else state)
 
 
 # ------------------------------------------------------------------ C ABI
@@ -214,9 +217,14 @@ def md_bind_layout(ctx, env_offsets):
 def md_step(ctx, state, action, action_per_step, obs=None, n_obs_slots=0, n_steps=1, step0=0,
             stream=None):
     """state: DeviceState (or md_state); action/obs: CUDA float32 tensors."""
-    st = lib().md_step(ctx, _state_arg(state), action.data_ptr(), 1 if action_per_step else 0,
-                       None if obs is None else obs.data_ptr(), int(n_obs_slots),
-                       int(n_steps), int(step0), _stream_ptr(stream))
+    step = lib().md_step
+    if type(state) is DeviceState:
+        step, s = _packed_step, state.pointers()
+    else:
+        s = ctypes.byref(state.as_md_state() if hasattr(state, "as_md_state") else state)
+    st = step(ctx, s, action.data_ptr(), 1 if action_per_step else 0,
+              None if obs is None else obs.data_ptr(), int(n_obs_slots),
+              int(n_steps), int(step0), _stream_ptr(stream))
     if st != MD_OK:
         check(st, ctx)
 
