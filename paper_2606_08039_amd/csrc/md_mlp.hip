@@ -226,7 +226,8 @@ struct DgradArgs {
     const bf16 *W;
     const float *Z;
     bf16 *dZ;
-    float *part_b, *loss_part;
+    float *part_b;
+    double *loss_part;
 };
 
 // Gradient of the mean squared error over B x OUT standardised targets, and
@@ -244,7 +245,8 @@ __global__ void __launch_bounds__(256, 2) mlp_dgrad_kernel(DgradArgs a) {
     constexpr int LDY = 40;
     __shared__ __attribute__((aligned(16))) bf16 dy[16 * LDY];
     __shared__ __attribute__((aligned(16))) bf16 ds[2][16 * LDH];
-    __shared__ float red[2][96];
+    __shared__ float red4[96];
+    __shared__ double red[96];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
     // the outputs padded to k = 32: the padding alone, since the outputs'
     // elements are written by other threads before the first barrier
@@ -268,7 +270,9 @@ __global__ void __launch_bounds__(256, 2) mlp_dgrad_kernel(DgradArgs a) {
     const bool out_thread = tid < 16 * MLP_OUT;
     const float ym = a.norm[2 * MLP_IN + yo], ys = a.norm[2 * MLP_IN + MLP_OUT + yo];
     const float scale = 2.f / (float)(a.B * MLP_OUT);
-    float e2 = 0.f, sum4 = 0.f, sums[3][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+    // (squared errors in double: a workgroup's chain grows with the batch)
+    double e2 = 0.0;
+    float sum4 = 0.f, sums[3][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
     for (int tile = blockIdx.x; tile < a.tiles; tile += gridDim.x) {
         const int b0 = 16 * tile;
         f32x4 z[3][2];
@@ -284,7 +288,7 @@ __global__ void __launch_bounds__(256, 2) mlp_dgrad_kernel(DgradArgs a) {
                 const float ts = (a.T[b * MLP_OUT + yo] - ym) / ys;
                 const float d = a.Y[b * MLP_OUT + yo] - ts;
                 gy = d * scale;
-                e2 += d * d;
+                e2 += (double)(d * d);
             }
             sum4 += gy;
             dy[yr * LDY + yo] = (bf16)gy;
@@ -329,17 +333,17 @@ __global__ void __launch_bounds__(256, 2) mlp_dgrad_kernel(DgradArgs a) {
             if (g == 0) pb[MLP_H * l + 32 * w + 16 * j + r] = s;
         }
     if (out_thread) {
-        red[0][tid] = sum4;
-        red[1][tid] = e2;
+        red4[tid] = sum4;
+        red[tid] = e2;
     }
     __syncthreads();
     if (tid < MLP_OUT) {
         float s = 0.f;
-        for (int k = 0; k < 16; ++k) s += red[0][k * MLP_OUT + tid];
+        for (int k = 0; k < 16; ++k) s += red4[k * MLP_OUT + tid];
         pb[3 * MLP_H + tid] = s;
     } else if (tid == 64) {
-        float s = 0.f;
-        for (int k = 0; k < 96; ++k) s += red[1][k];
+        double s = 0.0;
+        for (int k = 0; k < 96; ++k) s += red[k];
         a.loss_part[blockIdx.x] = s;
     }
 }
@@ -526,7 +530,8 @@ struct md_mlp {
     bf16 *act = nullptr;
     float *Z = nullptr, *Y = nullptr;
     bf16 *dZ = nullptr;  // operands of the weight gradients, [units][batch]
-    float *part = nullptr, *part_b = nullptr, *loss_part = nullptr;
+    float *part = nullptr, *part_b = nullptr;
+    double *loss_part = nullptr;
     int last_B = 0, loss_parts = 0, fwd_B = 0;
     bool have_fwd = false, have_bwd = false;
     std::vector<void *> allocs;
@@ -782,10 +787,10 @@ md_status md_mlp_loss(const md_mlp *m, double *out) {
     if (!m || !out) return MD_E_INVALID_ARG;
     if (!m->have_bwd) return MD_E_INVALID_ARG;
     (void)hipDeviceSynchronize();
-    std::vector<float> h(m->loss_parts);
-    if (hipMemcpy(h.data(), m->loss_part, sizeof(float) * h.size(), hipMemcpyDeviceToHost) != hipSuccess) return MD_E_HIP;
+    std::vector<double> h(m->loss_parts);
+    if (hipMemcpy(h.data(), m->loss_part, sizeof(double) * h.size(), hipMemcpyDeviceToHost) != hipSuccess) return MD_E_HIP;
     double s = 0.0;
-    for (float v : h) s += v;
+    for (double v : h) s += v;
     *out = s / ((double)m->last_B * md::MLP_OUT);
     return MD_OK;
 }
