@@ -436,7 +436,8 @@ md_status md_mlp_get_norm(const md_mlp *m, float *h_norm);
 
 /* Forward pass of B <= max_batch samples: d_X [B][64] raw features (fp32,
  * device).  Keeps the activations for md_mlp_backward.  d_Y (nullable):
- * [B][6] de-standardised outputs (fp32, device).  Asynchronous on stream. */
+ * [B][6] de-standardised outputs (fp32, device), which may overlap d_X.
+ * Asynchronous on stream. */
 md_status md_mlp_forward(md_mlp *m, const float *d_X, int B, float *d_Y, void *stream);
 
 /* md_mlp_forward for callers that cannot allocate device memory: code under
@@ -447,7 +448,8 @@ md_status md_mlp_forward(md_mlp *m, const float *d_X, int B, float *d_Y, void *s
  * same outputs), with every intermediate on chip.  Calls no allocator and
  * writes nothing but d_Y: calls that overlap in time (other streams, other
  * host threads) do not disturb one another, and md_mlp_backward still refers
- * to the last md_mlp_forward.  Asynchronous on stream (a stream of m's
+ * to the last md_mlp_forward.  d_Y may overlap d_X; such calls pass through a
+ * buffer of m and are the ones that must not overlap one another in time.  Asynchronous on stream (a stream of m's
  * device).  MD_E_INVALID_ARG for a null pointer, B < 0 or
  * B > MD_MLP_NOALLOC_MAX_BATCH. */
 #define MD_MLP_NOALLOC_MAX_BATCH 4096

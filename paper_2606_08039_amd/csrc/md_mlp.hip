@@ -488,6 +488,16 @@ __device__ __forceinline__ void store_operands(int i, float p, bf16 *Wf, bf16 *W
     }
 }
 
+// Outputs from a buffer of the network's to the caller's, de-standardised with
+// norm (not null) as the forward kernel does it: for outputs that overlap the
+// inputs, which other workgroups may still be reading.
+__global__ void outputs_kernel(const float *src, const float *norm, float *out, long long n) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int o = (int)(i % MLP_OUT);
+    out[i] = norm ? src[i] * norm[2 * MLP_IN + MLP_OUT + o] + norm[2 * MLP_IN + o] : src[i];
+}
+
 __global__ void pack_kernel(const float *p, bf16 *Wf, bf16 *Wt) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < MLP_NPARAMS) store_operands(i, p[i], Wf, Wt);
@@ -529,6 +539,7 @@ struct md_mlp {
     // pre-activations in fragment order, the standardised outputs
     bf16 *act = nullptr;
     float *Z = nullptr, *Y = nullptr;
+    float *spare = nullptr;  // outputs of md_mlp_forward_noalloc that overlap its inputs
     bf16 *dZ = nullptr;  // operands of the weight gradients, [units][batch]
     float *part = nullptr, *part_b = nullptr;
     double *loss_part = nullptr;
@@ -595,6 +606,7 @@ md_status md_mlp_create(int max_batch, md_mlp **out) {
     A(&m->act, Bm * md::ACT_ROWS);
     A(&m->Z, Bm * 3 * md::MLP_H);
     A(&m->Y, Bm * md::MLP_OUT);
+    A(&m->spare, (size_t)MD_MLP_NOALLOC_MAX_BATCH * md::MLP_OUT);
     A(&m->dZ, Bm * md::DZ_ROWS);
     A(&m->part, (size_t)md::max_slices(max_batch) * md::MLP_NPARAMS);
     A(&m->part_b, (size_t)md::DGRAD_MAX_WG * md::NBIAS);
@@ -690,12 +702,18 @@ hipError_t mlp_forward_on(const md_mlp *m, const float *d_X, int B, bool keep, f
     a.act = m->act;
     a.Z = m->Z;
     a.Y = m->Y;
-    a.out = d_Y;
+    const long long n = (long long)B * MLP_OUT;
+    const uintptr_t x = (uintptr_t)d_X, y = (uintptr_t)d_Y;
+    const bool overlap = d_Y && y < x + sizeof(float) * B * MLP_IN && x < y + sizeof(float) * n;
+    a.out = !overlap ? d_Y : keep ? nullptr : m->spare;
     const int grid = std::min(a.tiles, FWD_MAX_WG);
     if (keep)
         hipLaunchKernelGGL(mlp_forward_kernel<true>, dim3(grid), dim3(256), 0, st, a);
     else
         hipLaunchKernelGGL(mlp_forward_kernel<false>, dim3(grid), dim3(256), 0, st, a);
+    if (overlap)
+        hipLaunchKernelGGL(outputs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, keep ? m->Y : m->spare,
+                           keep ? m->norm : nullptr, d_Y, n);
     return hipGetLastError();
 }
 
