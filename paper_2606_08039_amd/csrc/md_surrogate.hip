@@ -276,7 +276,8 @@ __device__ __forceinline__ void features_self(const KConst &c, const Drone &d, c
 
 // The next 48: 8 x (dp, dv) of the nearest neighbours (world frame).  A
 // missing neighbour is the drone's own slot: its differences are exactly 0,
-// and no input needs a select or a branch.
+// and no input needs a select or a branch.  Only where the drone's own state is
+// not finite (own_finite) they are not; the callers then put the zeros in.
 __device__ __forceinline__ void features_neighbours(const Drone &d, const float4 *pos, const float4 *vel,
                                                     const int bj[KNN], float *f) {
 #pragma unroll
@@ -289,6 +290,10 @@ __device__ __forceinline__ void features_neighbours(const Drone &d, const float4
         f[6 * t + 4] = vj.y - d.vy;
         f[6 * t + 5] = vj.z - d.vz;
     }
+}
+
+__device__ __forceinline__ bool own_finite(const Drone &d) {
+    return fabsf(d.px + d.py + d.pz + d.vx + d.vy + d.vz) < __builtin_inff();
 }
 
 // The last 6: z, ground proximity (h_clip / max(z, h_clip))^2, 0-pad.
@@ -739,6 +744,22 @@ __global__ void __launch_bounds__(MAX_SLOTS) sur_step_kernel(SurArgs sa) {
                 }
                 *(bf16x8 *)(row + k) = v;
             }
+            // missing neighbours of a drone that is not finite: the input 0
+            if (__ballot(!own_finite(d)) != 0ull) {
+#pragma unroll 1
+                for (int t = 0; t < KNN; ++t) {
+                    int j = bj[0];
+#pragma unroll
+                    for (int u = 1; u < KNN; ++u) j = t == u ? bj[u] : j;
+                    if (j != slot) continue;
+#pragma unroll
+                    for (int k = 0; k < 6; k += 2) {
+                        const float4 m = xnorm[(10 + 6 * t + k) / 2];
+                        row[10 + 6 * t + k] = (bf16)m.y;
+                        row[10 + 6 * t + k + 1] = (bf16)m.w;
+                    }
+                }
+            }
         }
         __syncthreads();
         mlp_wave(feat + wbase * FEAT_STRIDE, (float *)(feat + wbase * FEAT_STRIDE), sa.W, sa.b, lane);
@@ -910,6 +931,9 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     for (int t = 0; t < KNN; ++t) nj[t] = bj[t] >= 0 ? bj[t] : slot;
     features_self(c, d, R, n, f);
     features_neighbours(d, pos, vel, nj, f + 10);
+    if (!own_finite(d))
+        for (int t = 0; t < KNN; ++t)
+            for (int k = 0; k < 6; ++k) f[10 + 6 * t + k] = bj[t] >= 0 ? f[10 + 6 * t + k] : 0.f;
     features_tail(c, d, f + 58);
     // drone (lane / 4) + 16 i of the wave is stored by lanes 4 (lane / 4) .. + 3
     int dst[4];
