@@ -880,7 +880,9 @@ constexpr int STAGE_ROW = 20;
 // 64-byte request), and environments of up to 64 drones rank by keys.  262144
 // drones in environments of 32: 37.5 -> 27.6 us; what is left above the
 // memory's time is one round of load, compute and store per wave, all 4096
-// resident at once.
+// resident at once.  Waves with tied distances rank twice: on regular grids
+// 262144 drones in environments of 32 took 38.5 -> 32.2 us, of 16 32.9 -> 23.2,
+// of 64 50.0 -> 51.5 (where the positions scatter, 51 -> 47).
 __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     const KConst &c = g.c;
     const int S = blockDim.x;
