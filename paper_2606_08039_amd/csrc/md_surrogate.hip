@@ -933,9 +933,6 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     for (int t = 0; t < KNN; ++t) nj[t] = bj[t] >= 0 ? bj[t] : slot;
     features_self(c, d, R, n, f);
     features_neighbours(d, pos, vel, nj, f + 10);
-    if (!own_finite(d))
-        for (int t = 0; t < KNN; ++t)
-            for (int k = 0; k < 6; ++k) f[10 + 6 * t + k] = bj[t] >= 0 ? f[10 + 6 * t + k] : 0.f;
     features_tail(c, d, f + 58);
     // drone (lane / 4) + 16 i of the wave is stored by lanes 4 (lane / 4) .. + 3
     int dst[4];
@@ -960,6 +957,12 @@ __global__ void __launch_bounds__(MAX_SLOTS) datagen_kernel(GenArgs g) {
     float Fx, Fy, Fz;
     plain_aero(c, g.mask, d, R, n, T, pos, lo, menv, mmax, Fx, Fy, Fz);
     if (!valid) return;
+    if (!own_finite(d)) {
+        __threadfence();  // after this drone's row, which other lanes stored
+        for (int t = 0; t < KNN; ++t)
+            for (int k = 0; k < 6; ++k)
+                if (bj[t] < 0) g.X[(long long)di * MLP_IN + 10 + 6 * t + k] = 0.f;
+    }
     float *y = g.Y + (long long)di * MLP_OUT;
     y[0] = R.r00 * Fx + R.r10 * Fy + R.r20 * Fz;
     y[1] = R.r01 * Fx + R.r11 * Fy + R.r21 * Fz;
