@@ -44,7 +44,7 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // Measured without -> with the tests: 512 x 256 drones, 50
 // steps, block sweep 617 -> 395 us; 4096 x 64, 60 steps, rotation sweep with
 // observations 433 -> 325 us, without 377 -> 240 us; 8192 x 32, 60 steps with
-// observations 300 -> 284 us.  Lattices drawn together to 0.3 of their pitch,
+// observations 299 -> 288 us.  Lattices drawn together to 0.3 of their pitch,
 // where the tests are given up: 512 x 256 946 (all pairs) -> 682 us, 2048 x 64 with
 // observations 340 -> 329 us, without 303 -> 303 us, 8192 x 32 257 -> 252 us, 4096 x
 // 32 under wind 245 -> 244 us, Runge-Kutta 2048 x 64, 40 steps 618 -> 562 us.
@@ -53,7 +53,7 @@ __device__ __forceinline__ KConst margin_consts(const KConst &c) {
 // environment (or of the wave) has moved MEMO_MOVE, with a radius that allows
 // for it, and evaluate a few pairs more instead of testing all.  A pair that
 // is evaluated needlessly adds its exact 0.  Formed at every step -> kept: 512
-// x 256 drones, 50 steps 394 -> 175 us, Runge-Kutta 256 x 256, 20 steps 572 ->
+// x 256 drones, 50 steps 394 -> 176 us, Runge-Kutta 256 x 256, 20 steps 572 ->
 // 258 us; 2048 x 64, 60 steps with observations 200 -> 167 us, without 178 ->
 // 140 us; 4096 x 32 randomised, 50 steps 333 -> 312 us.
 constexpr int SPARSE_RETRY = 32;
@@ -497,7 +497,7 @@ __device__ __forceinline__ float dw_pairs_rot_batched(const KConst &c0, const fl
 // ascending.  KEEP: the outcomes are kept until a drone has moved.  The Euler
 // step of 32 drones runs its sixteen tests every time, which costs no more
 // than keeping their outcomes (8192 x 32 drones, 60 steps with observations:
-// 276 us run, 284-300 us kept; 2048 x 64 178 run, 139 us kept).  The stages of
+// 3-8 % longer with kept ones; 2048 x 64 178 run, 139 us kept).  The stages of
 // a Runge-Kutta step lie close together and keep them (50 steps, every pair
 // evaluated -> kept: 8192 x 32 690 -> 593 us, 4096 x 32 421 -> 418 us, 2048 x
 // 64 641 -> 415 us).
@@ -609,10 +609,10 @@ __device__ __forceinline__ float dw_rot(const KConst &c, const float4 *own, int 
 // term costs a compare, a select, an add and a rotation more.
 // The order of a drone's sum depends only on its place in its environment.
 // 512 environments x 256 drones, 50 steps: 895 us with the all-pairs sweep,
-// 617 us with every pair of this one evaluated, 175 us with tests that are
-// kept; with every pair evaluated it is bound by the vector ALU (busy 89 % of
-// the time at the two waves per SIMD that this layout gives, 4.4 cycles an
-// instruction).
+// 617 us with every pair of this one evaluated, 176 us with tests that are
+// kept.  What bounds it then is the step of one wave, with two waves per SIMD
+// in this layout: the vector ALU is active for a third of a wave's cycles
+// (counters over 1500 steps of flight).
 // dw_block sweeps and writes the sums for other waves; after a barrier
 // dw_block_rest adds those that other waves left for this one.
 //
