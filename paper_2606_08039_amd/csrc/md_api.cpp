@@ -360,9 +360,9 @@ LaunchPlan plan_for(const md_ctx *ctx, const LaunchCfg &cfg) {
 //   envs, 375 steps 1.59 / 1.67 / 1.50, 750 3.22 / 3.34 / 2.98
 //   wind 8192 envs, 250 steps 1.66 / 1.66 / 1.64, 500 3.53 / 3.57 / 3.42, 1000
 //   7.32 / 7.23 / 6.73; 6500 envs, 500 3.34 / 3.42 / 3.23
-//   Runge-Kutta 8192 envs, 60 steps 0.84 / 0.88 / 0.93, 500 7.90 / 7.44 / 7.65,
-//   1000 15.6 / 14.8 / 15.3; 6500 envs, 1000 15.2 / 14.5 / 15.2; of 16: 16384
-//   envs, 1000 10.4 / 10.6 / 10.3
+//   Runge-Kutta 8192 envs, 60 steps 0.84 / 0.88 / 0.93, 250 3.64 / 3.58, 375 5.56 /
+//   5.34, 1000 15.0 / 14.4 / 15.1; 6500 envs, 375 5.48 / 5.26; of 64: 4096 envs, 250
+//   steps 3.11 / 2.99; of 16: 16384 envs, 1000 10.4 / 10.6 / 10.3
 //   randomised 4096 envs, 250 steps 3.0 / 3.3, 8192 6.1 / 6.1, 12000 8.7 / 9.2
 // Without rows the two differ by 2 % at most, randomised by 10 % for one wave.
 // Where a group's granularity puts more waves on a SIMD than waves of their own
@@ -385,10 +385,9 @@ static long long rotation_waves_per_simd(const md_ctx *ctx, int group) {
 }
 
 static int rotation_waves(const md_ctx *ctx, int waves, bool rows, int n_steps) {
-    constexpr int LONG = 500;
     const bool rk4 = ctx->integ == MD_INTEG_RK4;
-    const int group = rk4 ? 8 : 16;
-    if (waves < group || !rows || n_steps < LONG || ctx->dr_on || (rk4 && ctx->max_m < 32)) return 1;
+    const int group = rk4 ? 8 : 16, from = rk4 ? 250 : 500;  // waves, steps
+    if (waves < group || !rows || n_steps < from || ctx->dr_on || (rk4 && ctx->max_m < 32)) return 1;
     const long long apart = rotation_waves_per_simd(ctx, 1);
     return apart >= WAVES_FULL && rotation_waves_per_simd(ctx, group) <= apart ? group : 1;
 }

@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(1024) rk4_kernel(StepArgs a) {
             const float h = (st < 2) ? half_dt : c.dt;
 #define MD_RK_FIELD(f)              \
     ks.f += wgt * k.f;              \
-    if (st < 3) d.f = x0.f + h * k.f;
+    d.f = x0.f + h * k.f;
             MD_RK_FIELD(px) MD_RK_FIELD(py) MD_RK_FIELD(pz)
             MD_RK_FIELD(vx) MD_RK_FIELD(vy) MD_RK_FIELD(vz)
             MD_RK_FIELD(qw) MD_RK_FIELD(qx) MD_RK_FIELD(qy) MD_RK_FIELD(qz)

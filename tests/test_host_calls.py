@@ -217,7 +217,7 @@ for args, want in [((8192, 32, 500, 16), 16), ((8192, 32, 499, 16), 1), ((8192, 
                    ((6146, 32, 1000, 16), 16), ((8193, 32, 1000, 16), 1), ((12000, 32, 1000, 16), 1),
                    ((16384, 32, 1000, 16), 16), ((4096, 64, 1000, 16), 16), ((16384, 16, 1000, 16), 16),
                    ((100, 32, 1000, 16), 1), ((8192, 32, 1000, 16, WIND), 16), ((8192, 32, 1000, 8, DR), 1),
-                   ((8192, 32, 500, 16, RK4), 8), ((8192, 32, 500, 8, RK4), 8), ((8192, 32, 500, 4, RK4), 1),
+                   ((8192, 32, 250, 16, RK4), 8), ((8192, 32, 249, 16, RK4), 1), ((8192, 32, 500, 8, RK4), 8), ((8192, 32, 500, 4, RK4), 1),
                    ((12000, 32, 500, 16, RK4), 8), ((10000, 32, 500, 16, RK4), 1), ((16384, 16, 500, 16, RK4), 1)]:
     got = blocks(*args)
     assert got == want, (args, got, want)
