@@ -771,8 +771,13 @@ __device__ __forceinline__ float dw_block(const KConst &c0, const float4 *pos, f
                 }
             }
             memo.need = words;
-            // 32 W shifts were tested
-            dense = count > 16 * W ? SPARSE_RETRY + 1 : 0;
+            // 32 W shifts were tested; one after the other, twelve W take about
+            // as long as all of them in batches (30 steps, limit 8 W / 12 W / 16 W,
+            // lattices at 0.7 and 0.35 of their pitch: 11 x 256 drones 160 / 160 /
+            // 160 and 288 / 290 / 337 us, 390 x 256 307 / 362 / 395 and 399 / 404 /
+            // 454, 15 x 192 222 / 141 / 141 and 218 / 231 / 231, 520 x 192 under
+            // Runge-Kutta 1127 / 909 / 910 and 1496 / 1490 / 1490)
+            dense = count > 12 * W ? SPARSE_RETRY + 1 : 0;
         }
     }
     memo.dense = max(dense - 1, 0);
